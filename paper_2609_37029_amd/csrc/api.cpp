@@ -135,8 +135,10 @@ struct ldr_views {
   uint8_t* arena;
   int64_t* pos;
   const void* G;
-  int32_t* status;  // device, 256 bytes: the sticky flags, and at word
-                    // kCommitCounter the update's commit counter
+  int32_t* status;  // device: the sticky flags, and from word kCommitCounter the
+                    // update's commit counters
+  void* scratch;    // device: partial statistics of long updates (behind the status
+                    // block, one allocation), or null
 };
 
 extern "C" {
@@ -207,11 +209,12 @@ static int views_update_impl(ldr_views* v, const int32_t* n_new, int32_t max_new
   if (max_new > 0 && (!K_new || !V_new || !aligned(K_new, 16) || !aligned(V_new, 16)))
     return LDR_EINVAL;
   if (v->s.keep_bnd && (!h_new || !aligned(h_new, 16))) return LDR_EINVAL;
-  // the last launch that reads t commits from its last workgroup
+  // the last launch that reads t commits, each sequence from its last workgroup
   int32_t* done = v->status + kCommitCounter;
   if (max_new > 0) {
     if (launch_views_update(v->s, v->L, v->batch, v->arena, v->pos, v->G, n_new, max_new, K_new,
-                            V_new, h_new, st, v->status, v->s.P ? nullptr : done) != hipSuccess)
+                            V_new, h_new, st, v->status, v->s.P ? nullptr : done,
+                            v->scratch) != hipSuccess)
       return LDR_EHIP;
     if (v->s.P && launch_views_pool(v->s, v->L, v->batch, v->arena, v->pos, n_new, max_new,
                                     K_new, V_new, st, v->status, done) != hipSuccess)
@@ -238,12 +241,24 @@ int ldr_views_init(ldr_views** out, const ldr_config* cfg, int32_t batch, void* 
   if (!v) return LDR_ENOMEM;
   v->cfg = *cfg; v->s = s; v->L = make_layout(s); v->batch = batch;
   v->arena = static_cast<uint8_t*>(arena); v->pos = pos; v->G = G; v->status = nullptr;
-  if (hipMalloc(reinterpret_cast<void**>(&v->status), 256) != hipSuccess) {
+  v->scratch = nullptr;
+  // One allocation: the status block, then the scratch of long updates. Without
+  // room for the scratch, updates run unsplit (the failed call's error is cleared).
+  const size_t sb = views_scratch_bytes(s, batch), fb = views_status_bytes(batch);
+  if (sb > 0) {
+    if (hipMalloc(reinterpret_cast<void**>(&v->status), fb + sb) == hipSuccess) {
+      v->scratch = reinterpret_cast<uint8_t*>(v->status) + fb;
+    } else {
+      v->status = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  if (!v->status && hipMalloc(reinterpret_cast<void**>(&v->status), fb) != hipSuccess) {
     delete v;
     return LDR_ENOMEM;
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (hipMemsetAsync(v->status, 0, 256, st) != hipSuccess ||
+  if (hipMemsetAsync(v->status, 0, fb, st) != hipSuccess ||
       launch_views_reset(s, v->L, batch, arena, pos, st) != hipSuccess) {
     ldr_views_destroy(v);
     return LDR_EHIP;

@@ -149,14 +149,17 @@ __device__ inline bool in_support(const TopK& t, float z, int v) {
 // Views (views.hip)
 hipError_t launch_views_reset(const Shape& s, const Layout& L, int batch, void* arena,
                               int64_t* pos, hipStream_t st);
-// done: a device counter (0 between launches) when this launch commits
-// (advances pos, or flags a bad count in status) from its last workgroup;
-// null when a later launch reads pos and commits instead.
+// done: the sequences' device counters (0 between launches) when this launch
+// commits (advances pos, or flags a bad count in status) from the last workgroup
+// of each sequence; null when a later launch reads pos and commits instead.
 hipError_t launch_views_update(const Shape& s, const Layout& L, int batch, void* arena,
                                int64_t* pos, const void* G, const int32_t* n_new,
                                int max_new, const void* K_new, const void* V_new,
                                const void* h_new, hipStream_t st, int32_t* status,
-                               int32_t* done);
+                               int32_t* done, void* scratch);
+// Scratch of the launch above for `batch` sequences (0: none needed). With null
+// scratch an update's rows are not split over workgroups.
+size_t views_scratch_bytes(const Shape& s, int batch);
 // Mean-pooled summary banks (views.hip); runs after the update, before the
 // commit (done as above).
 hipError_t launch_views_pool(const Shape& s, const Layout& L, int batch, void* arena,
@@ -239,9 +242,13 @@ struct DraftPtrs {
 // Bits of the sticky device status word.
 constexpr int kFlagRange = 1;   // an update saw a row count outside [0, max_new]
 constexpr int kFlagAnchor = 2;  // a draft step saw an anchor outside [0, V)
-// Word of the views' 256-byte status block (its own 64-byte line) that counts
-// the workgroups of an update launch done (0 between launches).
-constexpr int kCommitCounter = 16;
+// The views' status block: 256 bytes with the sticky flags, then a counter per
+// sequence (each on its own 64-byte line) of the workgroups of an update launch
+// that are done (0 between launches).
+constexpr int kCommitCounter = 64, kCommitStride = 16;   // words
+inline size_t views_status_bytes(int batch) {
+  return align_up((size_t)(kCommitCounter + batch * kCommitStride) * 4);
+}
 // Attention over [block; window; summary] of one layer (Eq. 6).
 struct AttnArgs {
   const void* qkv;   // block q, k, v rows (dtype) [M][qkv_out], normalised and rotated

@@ -9,12 +9,12 @@
 //    statistics of the new set N (Eq. 10) by a tiled online log-sum-exp over
 //    the rows, then the two-way merge with the stored (eta, m) (Eq. 11);
 //  * a slice of the boundary-state copy.
-// The commit then advances t (or raises the sticky range flag): the last
-// workgroup of the last kernel that reads t does it, once every other
-// workgroup of that launch has counted itself done on a device counter (each
-// counts after its own reads of t), so every workgroup reads the old t and
-// no separate launch is needed; without new rows a one-thread-per-sequence
-// commit kernel does it.
+// The commit then advances t (or raises the sticky range flag): in the last
+// kernel that reads t, the last workgroup of a sequence does it, once every
+// other workgroup of that sequence has counted itself done on the sequence's
+// device counter (each counts after its own reads of t), so every workgroup
+// reads the old t and no separate launch is needed; without new rows a
+// one-thread-per-sequence commit kernel does it.
 #include "ldr_internal.h"
 
 namespace ldr {
@@ -39,28 +39,32 @@ views_reset_kernel(uint8_t* arena, size_t stride, size_t eta_off, size_t eta_byt
     for (int b = threadIdx.x; b < batch; b += kThreads) pos[b] = 0;
 }
 
-// The commit by the last workgroup of a launch (done == null: not this launch).
+// The commit of a sequence by the last of its workgroups in a launch (done ==
+// null: not this launch). Each sequence has a counter on a line of its own: one
+// counter for the whole launch takes an atomic of every workgroup in turn, which
+// cost 9 us of the pooled update of 17 rows (1280 workgroups, 24.2 -> 15.6 us).
 struct CommitTail {
-  int32_t* done;      // device counter, 0 between launches
-  int total;          // workgroups of the launch
-  int64_t* pos; const int32_t* n_new; int max_new, batch; int32_t* status;
+  int32_t* done;      // device counters, kCommitStride words apart, 0 between launches
+  int total;          // workgroups of the launch per sequence
+  int64_t* pos; const int32_t* n_new; int max_new; int32_t* status;
 };
 
-__device__ void commit_tail(const CommitTail& c) {
+__device__ inline void commit(const CommitTail& c, int b) {
+  const int n = c.n_new[b];
+  if (n < 0 || n > c.max_new)
+    atomicOr(c.status, kFlagRange);
+  else
+    c.pos[b] += n;
+}
+
+__device__ void commit_tail(const CommitTail& c, int b) {
   if (!c.done) return;
-  __shared__ int last;
   __syncthreads();   // every thread of the workgroup is past its reads of t
-  if (threadIdx.x == 0) last = atomicAdd(c.done, 1) == c.total - 1;
-  __syncthreads();
-  if (!last) return;
-  for (int b = (int)threadIdx.x; b < c.batch; b += (int)blockDim.x) {
-    const int n = c.n_new[b];
-    if (n < 0 || n > c.max_new)
-      atomicOr(c.status, kFlagRange);
-    else
-      c.pos[b] += n;
-  }
-  if (threadIdx.x == 0) atomicExch(c.done, 0);   // ready for the next launch
+  if (threadIdx.x != 0) return;
+  int32_t* done = c.done + b * kCommitStride;
+  if (atomicAdd(done, 1) != c.total - 1) return;
+  commit(c, b);
+  atomicExch(done, 0);   // ready for the next launch
 }
 
 struct UpdateArgs {
@@ -71,6 +75,8 @@ struct UpdateArgs {
   int keep_win, keep_sum, keep_bnd;         // views kept (ablation variants drop some)
   int Wx;                                   // rows per (layer, group) region (window first)
   float inv_sqrt_d;
+  int splits;                // row ranges per (group, layer, sequence) (bf16 kernel)
+  float* part; float* part_ml;   // splits > 1: the ranges' O [unit][split][query][d] and (m, l)
   CommitTail ct;
 };
 
@@ -103,6 +109,28 @@ __device__ inline void boundary_slice(const UpdateArgs& a, uint8_t* seq, int j, 
   T* hdst = reinterpret_cast<T*>(seq + a.h);
   const T* hsrc = reinterpret_cast<const T*>(a.h_new) + (size_t)b * a.hb_elems;
   for (int c = c0 + (int)threadIdx.x; c < c1; c += nthreads) copy16(hdst, hsrc, c);
+}
+
+// The same slice in two parts, for a kernel that has other work while the
+// loads are in flight: the first chunk of every thread is held in a register.
+struct BoundaryCopy { const uint4* src; uint4* dst; int c0, c1; uint4 first; };
+template <typename T>
+__device__ inline BoundaryCopy boundary_load(const UpdateArgs& a, uint8_t* seq, int j, int g,
+                                             int b) {
+  const int chunks = a.hb_elems * (int)sizeof(T) / 16;
+  const int wgs = a.D * a.hkv, wid = j * a.hkv + g, per = (chunks + wgs - 1) / wgs;
+  BoundaryCopy c;
+  c.dst = reinterpret_cast<uint4*>(seq + a.h);
+  c.src = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.h_new) +
+                                         (size_t)b * a.hb_elems);
+  c.c0 = wid * per + (int)threadIdx.x;
+  c.c1 = min(chunks, wid * per + per);
+  if (c.c0 < c.c1) c.first = c.src[c.c0];
+  return c;
+}
+__device__ inline void boundary_store(const BoundaryCopy& c, int nthreads) {
+  if (c.c0 < c.c1) c.dst[c.c0] = c.first;
+  for (int i = c.c0 + nthreads; i < c.c1; i += nthreads) c.dst[i] = c.src[i];
 }
 
 // DPT: dims of the head each thread owns; TPQ = d / DPT threads share one
@@ -263,242 +291,501 @@ __device__ __forceinline__ void views_update_body(const UpdateArgs& a) {
 template <typename T, int DPT>
 __global__ void __launch_bounds__(kThreads) views_update_kernel(UpdateArgs a) {
   views_update_body<T, DPT>(a);
-  commit_tail(a.ct);
+  commit_tail(a.ct, blockIdx.z);
 }
 
-// bf16 path on the matrix cores (v_mfma_f32_16x16x32_bf16). One wave per 16
-// summary queries of the group (NW = rep * R / 16 waves); per tile of up to 32
-// new rows, K rows (row-major) and V^T go to LDS as bf16, then
-//  * S = G K^T on the matrix cores: bf16 products are exact in fp32 and the
-//    sums are fp32, as on the vector path;
-//  * the online log-sum-exp per query in fp32 (row max and sum over the 16
-//    lanes of a C-layout row group with DPP);
-//  * O += P V with P split into two bf16 terms, hi = bf16(P) and
-//    lo = bf16(P - hi), so P enters with a relative error near 2^-17 rather
-//    than bf16's 2^-9 (two MFMAs per tile instead of one);
-// then the merge of Eq. 11 with the stored (eta, m), as on the vector path.
+// bf16 path on the matrix cores (v_mfma_f32_16x16x32_bf16).
+//
+// One compute wave per 16 summary queries of the group (NW = rep * R / 16) and
+// one loader wave, which only stages the new rows, 32 at a time, by DMA
+// (global_load_lds) into a ring of NB stages, K rows then V rows, both as they
+// lie in memory. (A decode step has one tile: its compute waves stage it
+// themselves, NB = 1.) The scores are formed transposed, S^T = K G^T, so that a lane
+// holds 8 keys of one query and its probabilities are already the B operand of
+// O^T = V^T P^T (the order of the contraction index is free as long as both
+// operands share it); the V^T operand comes from the row-major V tile by
+// transposing LDS reads (ds_read_b64_tr_b16). No operand is transposed through
+// LDS stores and no probability passes through LDS.
+//  * bf16 products are exact in fp32 and the sums are fp32, as on the vector
+//    path; P enters as two bf16 terms, hi = bf16(P) and lo = bf16(P - hi), so
+//    its relative error is near 2^-17 rather than bf16's 2^-9 (two MFMAs per
+//    tile instead of one);
+//  * the online log-sum-exp keeps, per query, a reference m (in log2 units)
+//    that moves only when a tile's largest score passes it by more than 8:
+//    l and O share it, so a stale reference changes nothing but their scale,
+//    and below that no lane exchange and no rescale is needed;
+//  * then the merge of Eq. 11 with the stored (eta, m), as on the vector path.
+// 16-byte chunk c of row r sits at chunk c ^ row_swz(r) (the DMA permutes its
+// source addresses), so that the 16-row fragment reads of K and the 8-row half
+// waves of the transposing reads of V each hit 64 distinct banks.
+//
+// Long updates of few sequences (prefill) leave most CUs without work at one
+// workgroup per (group, layer, sequence), so the rows are then also cut into
+// `splits` ranges of whole tiles: each workgroup writes its (m, l, O) to the
+// handle's scratch and views_merge_kernel combines them in order.
+//
+// What bounds it: the rows' stream from HBM once the loads run ahead of the
+// tiles. Qwen3-8B shape, a 4096-row chunk
+// of one sequence 350 -> 36 us (one workgroup per group and layer before), of 16
+// sequences 661 -> 319 us (4.6 TB/s; the loads alone, without any arithmetic,
+// take about as long), 17 rows of 16 sequences 20.4 -> 14.8 us.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
 
-__device__ inline bf16x8 frag8(const uint16_t* p) {
+__device__ inline bf16x8 frag8(const void* p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p));
 }
-__device__ inline void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+template <int N> __device__ inline void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-template <int DH, int NW>
-__device__ __forceinline__ void views_update_mfma_body(const UpdateArgs& a) {
-  constexpr int KT = 32, KS = DH / 32, NT = DH / 16, NTH = NW * 64;
-  constexpr int KLD = DH + 8, VLD = KT + 8;   // padded LDS rows (elements)
-  __shared__ __attribute__((aligned(16))) uint16_t Kt[KT * KLD];
-  __shared__ __attribute__((aligned(16))) uint16_t Vt[DH * VLD];
-  __shared__ __attribute__((aligned(16))) uint16_t Pt[NW][2][16 * VLD];
-  const int g = blockIdx.x, j = blockIdx.y, b = blockIdx.z;
+// Chunk permutation of LDS row r (rows of DH bf16, DH / 8 chunks of 16 bytes).
+template <int DH> __device__ inline int row_swz(int r) {
+  return DH == 128 ? ((r & 7) << 1) | ((r >> 3) & 1) : (((r >> 1) & 3) << 1) | ((r >> 3) & 1);
+}
+
+// Weights of the merge of (eta_a, m_a) with a new set of log-normaliser eta_n
+// (Eq. 11): m = wa m_a + wn m_n, and the merged eta. An empty A returns N.
+__device__ inline void merge_weights(float eta_a, float eta_n, float& wa, float& wn, float& eta) {
+  if (eta_a == -INFINITY) {
+    wa = 0.f; wn = 1.f; eta = eta_n;
+    return;
+  }
+  const float mu = fmaxf(eta_a, eta_n);
+  eta = mu + logf(expf(eta_a - mu) + expf(eta_n - mu));
+  wa = expf(eta_a - eta);
+  wn = expf(eta_n - eta);
+}
+
+constexpr float kLn2 = 0.693147180559945309f, kLog2e = 1.44269504088896341f;
+
+// SUM: the learned summary is kept (otherwise only the ring and the boundary
+// are written, from the first tile that holds a surviving row on). NB = 1: the
+// update has at most one tile (a decode step).
+template <int DH, int NW, int NB, bool SUM>
+__device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
+  constexpr int KT = kTileRows, KS = DH / 32, NT = DH / 16, NTH = NW * 64;
+  constexpr int CPR = DH / 8, ROWB = DH * 2;      // 16-byte chunks and bytes of a row
+  constexpr int MAT = KT * ROWB, STAGE = 2 * MAT; // bytes of a K or V tile, of a stage
+  constexpr int QI = MAT / 1024, RPI = 1024 / ROWB;   // DMA instructions a tile, rows each
+  __shared__ __attribute__((aligned(1024))) uint8_t sm[NB * STAGE];
+  const int g = blockIdx.x, j = blockIdx.y;
+  const int b = blockIdx.z / a.splits, sp = blockIdx.z - b * a.splits;
   const int n = a.n_new[b];
   if (n <= 0 || n > a.max_new) return;  // empty set: identity; bad count: commit flags it
   const int64_t t = a.pos[b];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  uint8_t* seq = a.arena + (size_t)b * a.stride;
+  // this workgroup's tiles
+  const int tiles = (n + KT - 1) / KT, per = (tiles + a.splits - 1) / a.splits;
+  const int t1 = min(tiles, (sp + 1) * per);
+  int t0 = sp * per;
+  if (!SUM) t0 = a.keep_win ? max(t0, max(0, n - a.W) / KT) : t1;
+  const int nt = t1 - t0;
+  const int nr_last = n - (tiles - 1) * KT;
+  const bool ragged = t1 == tiles && nr_last < KT;   // the last tile has padding rows
 
-  // the wave's queries: rows q0 .. q0 + 15 of G, M and eta (C layout: this
-  // lane holds rows q0 + lg * 4 + v, dims dt * 16 + lr)
-  const size_t q0 = ((size_t)j * a.hq + (size_t)g * a.rep) * a.R + (size_t)wave * 16;
-  float* Mq = reinterpret_cast<float*>(seq + a.m) + q0 * DH;
-  float* etaq = reinterpret_cast<float*>(seq + a.eta) + q0;
-  const bool sum = a.keep_sum, win = a.keep_win;
-  float ma[NT][4], eta_a[4];
+  const size_t rstride = (size_t)a.D * a.hkv * DH;
+  const size_t base = (size_t)b * a.max_new * rstride + (size_t)(j * a.hkv + g) * DH;
+  const uint16_t* Kn = static_cast<const uint16_t*>(a.K_new) + base;
+  const uint16_t* Vn = static_cast<const uint16_t*>(a.V_new) + base;
+  // DMA instructions [qa, qb) of a tile's K and V rows; in the ragged tile, rows
+  // past n repeat row n - 1
+  auto issue = [&](int buf, int tile, int qa, int qb) {
+    const int r0 = min(tile, t1 - 1) * KT;
+    const bool whole = r0 + KT <= n;
+    uint8_t* dst = sm + buf * STAGE;
+    const uint16_t* kb = Kn + (size_t)r0 * rstride;
+    const uint16_t* vb = Vn + (size_t)r0 * rstride;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    eta_a[v] = sum ? etaq[lg * 4 + v] : -INFINITY;
+    for (int q = qa; q < qb; ++q) {
+      const int r = q * RPI + lane / CPR;
+      const uint32_t row = whole ? r : min(r, n - 1 - r0);
+      const uint32_t off = row * (uint32_t)rstride + ((lane % CPR) ^ row_swz<DH>(r)) * 8;
+      __builtin_amdgcn_global_load_lds(
+          (__attribute__((address_space(1))) void*)(kb + off),
+          (__attribute__((address_space(3))) void*)(dst + q * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(
+          (__attribute__((address_space(1))) void*)(vb + off),
+          (__attribute__((address_space(3))) void*)(dst + MAT + q * 1024), 16, 0, 0);
+    }
+  };
+  if (NB > 1 && wave == NW) {   // the loader
+    if (nt <= 0) return;
 #pragma unroll
-    for (int dt = 0; dt < NT; ++dt)
-      ma[dt][v] = sum ? Mq[(size_t)(lg * 4 + v) * DH + dt * 16 + lr] : 0.f;
+    for (int st = 0; st < NB - 1; ++st) issue(st, t0 + st, 0, QI);
+    int buf = NB - 1;
+    for (int kt = 0; kt < nt; ++kt) {
+      wait_vmcnt<2 * QI * (NB > 1 ? NB - 2 : 0)>();   // stage kt has landed
+      __builtin_amdgcn_s_barrier();                   // and stage kt - 1 has been read
+      if (ragged && kt == nt - 1) __builtin_amdgcn_s_barrier();
+      issue(buf, t0 + kt + NB - 1, 0, QI);
+      buf = buf == NB - 1 ? 0 : buf + 1;
+    }
+    wait_vmcnt<0>();   // no DMA outlives the workgroup
+    return;
   }
-  bf16x8 gf[KS];   // A layout: query row lr, dims ks * 32 + lg * 8 ..
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) gf[ks] = bf16x8{};
-  if (sum) {
+  // one tile: every wave stages its share of it
+  if constexpr (NB == 1) {
+    if (nt > 0) {   // (0: neither summary nor window)
+      if constexpr (QI >= NW) {
+        issue(0, t0, wave * (QI / NW), (wave + 1) * (QI / NW));
+      } else if (wave < QI) {
+        issue(0, t0, wave, wave + 1);
+      }
+    }
+  }
+
+  uint8_t* seq = a.arena + (size_t)b * a.stride;
+  // the wave's queries: rows q0 .. q0 + 15 of G, M and eta (this lane: query
+  // q0 + lr, dims dt * 16 + lg * 4 .. + 3)
+  const size_t q0 = ((size_t)j * a.hq + (size_t)g * a.rep) * a.R + (size_t)wave * 16;
+  bf16x8 gf[KS];   // B layout: query lr, dims ks * 32 + lg * 8 ..
+  if constexpr (SUM) {
     const uint16_t* Gq = static_cast<const uint16_t*>(a.G) + (q0 + lr) * DH + lg * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) gf[ks] = frag8(Gq + ks * 32);
   }
-
-  if (a.keep_bnd) boundary_slice<uint16_t>(a, seq, j, g, b, NTH);
+  // the stored (eta, m): ahead of the tile in a decode step, whose time is this
+  // latency; after the tiles otherwise
+  float* Mq = reinterpret_cast<float*>(seq + a.m) + (q0 + lr) * DH + lg * 4;
+  float* etaq = reinterpret_cast<float*>(seq + a.eta) + q0 + lr;
+  f32x4 ma[NT];
+  float eta_a = -INFINITY;
+  auto load_stored = [&]() {
+    eta_a = *etaq;
+#pragma unroll
+    for (int dt = 0; dt < NT; ++dt) ma[dt] = *reinterpret_cast<const f32x4*>(Mq + dt * 16);
+  };
+  if constexpr (SUM && NB == 1) load_stored();
+  BoundaryCopy bc{};
+  if (NB == 1 && a.keep_bnd) bc = boundary_load<uint16_t>(a, seq, j, g, b);
 
   uint16_t* Kw = reinterpret_cast<uint16_t*>(seq + a.kw) + ((size_t)(j * a.hkv + g) * a.Wx) * DH;
   uint16_t* Vw = reinterpret_cast<uint16_t*>(seq + a.vw) + ((size_t)(j * a.hkv + g) * a.Wx) * DH;
-  const uint16_t* Kn = static_cast<const uint16_t*>(a.K_new);
-  const uint16_t* Vn = static_cast<const uint16_t*>(a.V_new);
+  const uint32_t tm = a.keep_win ? (uint32_t)(t % a.W) : 0u;
+  const float c2 = a.inv_sqrt_d * kLog2e;
+  const int krow = lr * ROWB, ksz = row_swz<DH>(lr);
+  const int vr = lg * 4 + (lr >> 2);
+  const int vrow = vr * ROWB + (lr & 1) * 8, vsz = ((lr >> 1) & 1) ^ row_swz<DH>(vr);
   f32x4 o[NT];
 #pragma unroll
   for (int dt = 0; dt < NT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m[4], l[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) { m[v] = -INFINITY; l[v] = 0.f; }
+  float m = -INFINITY, l = 0.f;   // of query lr; l: this lane's keys only
 
-  for (int r0 = 0; r0 < ((win || sum) ? n : 0); r0 += KT) {
-    const int nr = min(KT, n - r0);
-    __syncthreads();   // the previous tile's LDS reads are done
-    // stage the tile (rows past nr as zeros) and ring-write the K rows that survive
-    for (int i = tid; i < KT * (DH / 8); i += NTH) {
-      const int r = i / (DH / 8), c8 = (i % (DH / 8)) * 8;
-      u32x4 kv = u32x4{0u, 0u, 0u, 0u}, vv = kv;
-      if (r < nr) {
-        const size_t src = ((((size_t)b * a.max_new + r0 + r) * a.D + j) * a.hkv + g) * DH + c8;
-        kv = *reinterpret_cast<const u32x4*>(Kn + src);
-        vv = *reinterpret_cast<const u32x4*>(Vn + src);
-        if (win && r0 + r >= n - a.W) {
-          const size_t slot = (size_t)((t + r0 + r) % a.W);
-          *reinterpret_cast<u32x4*>(Kw + slot * DH + c8) = kv;
-        }
-      }
-      *reinterpret_cast<u32x4*>(&Kt[r * KLD + c8]) = kv;
-      const uint16_t* vp = reinterpret_cast<const uint16_t*>(&vv);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) Vt[(c8 + e) * VLD + r] = vp[e];
+  int buf = 0;
+  for (int kt = 0; kt < nt; ++kt) {
+    const int r0 = (t0 + kt) * KT, nr = min(KT, n - r0);
+    if constexpr (NB == 1) wait_vmcnt<0>();   // own share of the tile
+    else __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));   // own LDS reads of stage kt - 1
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    uint8_t* Kt = sm + buf * STAGE;
+    uint8_t* Vt = Kt + MAT;
+    if (ragged && kt == nt - 1) {   // padding rows of V are 0 (their probability is)
+      for (int i = tid; i < (KT - nr) * CPR; i += NTH)
+        *reinterpret_cast<u32x4*>(Vt + nr * ROWB + i * 16) = u32x4{0u, 0u, 0u, 0u};
+      lds_barrier();
     }
-    __syncthreads();
-    {  // window V^T: lanes take consecutive rows of one dim (contiguous slots)
+    if (a.keep_win && r0 + nr > n - a.W) {   // rows that survive in the ring
       const int rs = max(0, n - a.W - r0);
-      const int r = tid % KT;
-      if (win && r >= rs && r < nr) {
-        const size_t slot = (size_t)((t + r0 + r) % a.W);
-        for (int e = tid / KT; e < DH; e += NTH / KT) Vw[(size_t)e * a.Wx + slot] = Vt[e * VLD + r];
+      for (int i = rs * CPR + tid; i < nr * CPR; i += NTH) {
+        const int r = i / CPR, c = i % CPR;
+        const size_t slot = (tm + (uint32_t)(r0 + r)) % (uint32_t)a.W;
+        *reinterpret_cast<u32x4*>(Kw + slot * DH + c * 8) =
+            *reinterpret_cast<const u32x4*>(Kt + r * ROWB + ((c ^ row_swz<DH>(r)) * 16));
+      }
+      const int r = tid % KT;   // V^T: lanes take consecutive rows of one dim
+      if (r >= rs && r < nr) {
+        const size_t slot = (tm + (uint32_t)(r0 + r)) % (uint32_t)a.W;
+        for (int e = tid / KT; e < DH; e += NTH / KT)
+          Vw[(size_t)e * a.Wx + slot] = *reinterpret_cast<const uint16_t*>(
+              Vt + r * ROWB + (((e >> 3) ^ row_swz<DH>(r)) * 16) + (e & 7) * 2);
       }
     }
-    if (!sum) continue;   // window only: no statistics
-    // scores of keys nt * 16 + lr (C layout), scaled; keys past nr masked
-    f32x4 sc[2];
+    if constexpr (SUM) {
+      // raw scores of query lr with keys h * 16 + lg * 4 + v
+      f32x4 sc[2];
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      sc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int h = 0; h < 2; ++h) {
+        sc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        sc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            gf[ks], frag8(&Kt[(nt * 16 + lr) * KLD + ks * 32 + lg * 8]), sc[nt], 0, 0, 0);
+        for (int ks = 0; ks < KS; ++ks)
+          sc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              frag8(Kt + h * 16 * ROWB + krow + (((ks * 4 + lg) ^ ksz) * 16)), gf[ks], sc[h], 0, 0,
+              0);
+      }
+      if (nr < KT) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (h * 16 + lg * 4 + v >= nr) sc[h][v] = -INFINITY;
+      }
+      float cm = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
+                       fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3]))) * c2;
+      if (__ballot(cm > m + 8.f) != 0) {
+        cm = fmaxf(cm, __shfl_xor(cm, 16));
+        cm = fmaxf(cm, __shfl_xor(cm, 32));
+        const float mn = cm > m + 8.f ? cm : m;
+        const float alpha = mn == m ? 1.f : __builtin_amdgcn_exp2f(m - mn);   // first tile: 0
+        m = mn;
+        l *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt) o[dt] *= alpha;
+      }
+      bf16x8 phi, plo;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(sc[i >> 2][i & 3], c2, -m));
+        l += p;
+        phi[i] = (__bf16)p;
+        plo[i] = (__bf16)(p - (float)phi[i]);
+      }
+#pragma unroll
+      for (int dt = 0; dt < NT; ++dt) {
+        uint8_t* vp = Vt + vrow + ((vsz ^ (dt * 2)) * 16);
+        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) s16x4*)vp);
+        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) s16x4*)(vp + 16 * ROWB));
+        const bf16x8 vf = __builtin_bit_cast(
+            bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, phi, o[dt], 0, 0, 0);
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, plo, o[dt], 0, 0, 0);
+      }
     }
-    uint16_t* Ph = Pt[wave][0];
-    uint16_t* Pl = Pt[wave][1];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const float x0 = lr < nr ? sc[0][v] * a.inv_sqrt_d : -INFINITY;
-      const float x1 = 16 + lr < nr ? sc[1][v] * a.inv_sqrt_d : -INFINITY;
-      const float mn = fmaxf(m[v], max16(fmaxf(x0, x1)));
-      const float alpha = expf(m[v] - mn);   // m = -inf on the first tile: 0
-      const float p0 = expf(x0 - mn), p1 = expf(x1 - mn);
-      l[v] = l[v] * alpha + sum16(p0 + p1);
-      m[v] = mn;
-#pragma unroll
-      for (int dt = 0; dt < NT; ++dt) o[dt][v] *= alpha;
-      const uint16_t h0 = f32_to_bf16(p0), h1 = f32_to_bf16(p1);
-      const int row = (lg * 4 + v) * VLD;
-      Ph[row + lr] = h0;
-      Ph[row + 16 + lr] = h1;
-      Pl[row + lr] = f32_to_bf16(p0 - bf16_to_f32(h0));
-      Pl[row + 16 + lr] = f32_to_bf16(p1 - bf16_to_f32(h1));
-    }
-    wave_lds_fence();
-    const bf16x8 phi = frag8(&Ph[lr * VLD + lg * 8]);
-    const bf16x8 plo = frag8(&Pl[lr * VLD + lg * 8]);
-#pragma unroll
-    for (int dt = 0; dt < NT; ++dt) {
-      const bf16x8 vf = frag8(&Vt[(dt * 16 + lr) * VLD + lg * 8]);
-      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(phi, vf, o[dt], 0, 0, 0);
-      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo, vf, o[dt], 0, 0, 0);
-    }
+    buf = buf == NB - 1 ? 0 : buf + 1;
   }
-  if (!sum) return;
-  // eta_N = m + log l, m_N = O / l, merged with (eta_A, m_A) (Eq. 11)
+  if (NB > 1 && a.keep_bnd && sp == 0) bc = boundary_load<uint16_t>(a, seq, j, g, b);
+  boundary_store(bc, NTH);
+  if constexpr (SUM) {
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (a.splits > 1) {   // (m, l, O) of this range, 0 weight if it is empty
+      const size_t row = ((((size_t)b * a.D + j) * a.hkv + g) * a.splits + sp) * (NW * 16) +
+                         wave * 16 + lr;
+      float* po = a.part + row * DH + lg * 4;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const float eta_n = m[v] + logf(l[v]);
-    const float inv_l = 1.f / l[v];
-    float wa, wn, e;
-    if (eta_a[v] == -INFINITY) {  // empty A: the merge returns N
-      wa = 0.f; wn = inv_l; e = eta_n;
-    } else {
-      const float mu = fmaxf(eta_a[v], eta_n);
-      e = mu + logf(expf(eta_a[v] - mu) + expf(eta_n - mu));
-      wa = expf(eta_a[v] - e);
-      wn = expf(eta_n - e) * inv_l;
+      for (int dt = 0; dt < NT; ++dt) *reinterpret_cast<f32x4*>(po + dt * 16) = o[dt];
+      if (lg == 0)
+        *reinterpret_cast<float2*>(a.part_ml + row * 2) = make_float2(m, l);
+      return;
     }
+    // eta_N = m + log l, m_N = O / l, merged with (eta_A, m_A) (Eq. 11)
+    if constexpr (NB > 1) load_stored();
+    float wa, wn, e;
+    merge_weights(eta_a, m * kLn2 + logf(l), wa, wn, e);
+    wn *= 1.f / l;
 #pragma unroll
     for (int dt = 0; dt < NT; ++dt) {
-      const float mav = wa != 0.f ? ma[dt][v] : 0.f;
-      Mq[(size_t)(lg * 4 + v) * DH + dt * 16 + lr] = wa * mav + wn * o[dt][v];
+      f32x4 r;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) r[v] = (wa != 0.f ? wa * ma[dt][v] : 0.f) + wn * o[dt][v];
+      *reinterpret_cast<f32x4*>(Mq + dt * 16) = r;
     }
-    if (lr == 0) etaq[lg * 4 + v] = e;
+    if (lg == 0) *etaq = e;
   }
 }
 
-template <int DH, int NW>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3)))
-views_update_mfma_kernel(UpdateArgs a) {
-  views_update_mfma_body<DH, NW>(a);
-  commit_tail(a.ct);
+template <int DH, int NW, int NB, bool SUM>
+__global__ void __launch_bounds__((NB > 1 ? NW + 1 : NW) * 64)
+    __attribute__((amdgpu_waves_per_eu(NB > 1 ? 4 : 3))) views_rows_kernel(UpdateArgs a) {
+  views_rows_body<DH, NW, NB, SUM>(a);
+  commit_tail(a.ct, blockIdx.z / a.splits);
+}
+
+// Combines the row ranges' (m, l, O) of 8 (d 128) or 16 (d 64) queries in range
+// order and merges them with the stored (eta, m) (Eq. 11). Grid (group and
+// layer, query tile, sequence); a thread owns 4 dims of one query, the threads
+// of a query in one wave (so every one of them has read eta before one of them writes it).
+template <int DH>
+__global__ void __launch_bounds__(256) views_merge_kernel(UpdateArgs a) {
+  constexpr int C4 = DH / 4, QP = 256 / C4, U = 8;   // float4s a query, queries, ranges in flight
+  const int g = blockIdx.x % a.hkv, j = blockIdx.x / a.hkv, b = blockIdx.z;
+  const int n = a.n_new[b], nq = a.rep * a.R;
+  if (n > 0 && n <= a.max_new) {
+    uint8_t* seq = a.arena + (size_t)b * a.stride;
+    const size_t unit = ((size_t)b * a.D + j) * a.hkv + g;
+    const int q = blockIdx.y * QP + (int)threadIdx.x / C4, c = (int)threadIdx.x % C4;
+    const size_t row0 = unit * a.splits * nq + q;
+    const size_t qrow = ((size_t)j * a.hq + (size_t)g * a.rep) * a.R + q;
+    float* Mq = reinterpret_cast<float*>(seq + a.m) + qrow * DH + c * 4;
+    float* etaq = reinterpret_cast<float*>(seq + a.eta) + qrow;
+    const float eta_a = *etaq;
+    const f32x4 ma = *reinterpret_cast<const f32x4*>(Mq);
+    float m = -INFINITY, l = 0.f;
+    f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < a.splits; s0 += U) {
+      float2 ml[U];
+      f32x4 x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {   // ranges past the last one repeat it (weight 0)
+        const size_t row = row0 + (size_t)min(s0 + u, a.splits - 1) * nq;
+        ml[u] = *reinterpret_cast<const float2*>(a.part_ml + row * 2);
+        x[u] = *reinterpret_cast<const f32x4*>(a.part + row * DH + c * 4);
+      }
+      float mn = m;
+#pragma unroll
+      for (int u = 0; u < U; ++u) mn = fmaxf(mn, ml[u].x);
+      const float alpha = mn == m ? 1.f : __builtin_amdgcn_exp2f(m - mn);
+      m = mn;
+      l *= alpha;
+      o *= alpha;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (s0 + u >= a.splits) break;
+        const float w = __builtin_amdgcn_exp2f(ml[u].x - m);   // an empty range: 0
+        l += w * ml[u].y;
+        o += w * x[u];
+      }
+    }
+    float wa, wn, e;
+    merge_weights(eta_a, m * kLn2 + logf(l), wa, wn, e);
+    wn *= 1.f / l;
+    f32x4 r;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) r[v] = (wa != 0.f ? wa * ma[v] : 0.f) + wn * o[v];
+    *reinterpret_cast<f32x4*>(Mq) = r;
+    if (c == 0) *etaq = e;
+  }
+  // t was read by the launch before this one, and is not read here
+  if (a.ct.done && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) commit(a.ct, b);
 }
 
 // Mean-pooled summary (the views as the configurations word them): for each
 // of two strides S, slot c mod P of the bank holds the mean K and V row of
-// chunk c = rows [cS, (c+1)S). One workgroup per (kv group, layer, sequence);
-// thread (bank, e) owns dim e of one bank. The chunks the new rows touch are
-// summed in fp32 in row order, the open chunk continuing from its stored sums,
-// and each slot takes sum / rows so far; only the last P chunks are written
-// (older ones would be recycled by the same update). Slots are the bank rows
-// after the window rows of the (layer, group) region: K row-major, V
-// transposed, like the window.
+// chunk c = rows [cS, (c+1)S). The chunks the new rows touch are summed in fp32
+// in row order, the open chunk continuing from its stored sums, and each slot
+// takes sum / rows so far; only the last P chunks are written (older ones would
+// be recycled by the same update). Slots are the bank rows after the window
+// rows of the (layer, group) region: K row-major, V transposed, like the window.
+//
+// The chunks of a bank are independent: a team of d / EPC threads (16 bytes of K
+// and of V each) sums one chunk, and the teams of a workgroup take runs of
+// consecutive chunks, whose V means go through LDS so that the slots of a
+// dimension are written side by side (each team writing its own column, 2 bytes
+// a line, took 268 us for 1000 rows of 16 sequences, 178 now). The first
+// and the last chunk of a bank are in one run: the first may continue from the
+// stored sums of the open chunk, which the last replaces after the barrier.
 struct PoolArgs {
   uint8_t* arena; size_t stride, kw, vw, ps;
   const int64_t* pos; const int32_t* n_new; int max_new;
   const void* K_new; const void* V_new;
-  int D, hkv, d, Wr, Wx, P, S0, S1;
+  int D, hkv, d, Wr, Wx, P, S0, S1, zc;
   CommitTail ct;
 };
 
+// x / y and x % y for x >= 0, in 32 bits where x allows it (a 64-bit division
+// is some hundred instructions).
+__device__ inline int64_t div_pos(int64_t x, int y) {
+  return x <= 0x7fffffff ? (int64_t)((uint32_t)x / (uint32_t)y) : x / y;
+}
+__device__ inline int mod_pos(int64_t x, int y) { return (int)(x - div_pos(x, y) * y); }
+
 template <typename T>
 __device__ __forceinline__ void views_pool_body(const PoolArgs& a) {
-  const int g = blockIdx.x, j = blockIdx.y, b = blockIdx.z;
+  constexpr int EPC = 16 / sizeof(T), U = 8;   // elements a thread; rows in flight
+  constexpr int kMaxTeams = kThreads / (64 / EPC);
+  __shared__ __attribute__((aligned(16))) T Vs[kThreads * EPC];   // [team][d]
+  __shared__ int slots[kMaxTeams];
+  const int g = blockIdx.x, j = blockIdx.y, b = blockIdx.z / a.zc, z = blockIdx.z - b * a.zc;
   const int n = a.n_new[b];
   if (n <= 0 || n > a.max_new) return;   // empty set: identity; bad count: commit flags it
-  const int d = a.d, bank = (int)threadIdx.x / d, e = (int)threadIdx.x % d;
-  const int64_t t = a.pos[b], S = bank ? a.S1 : a.S0;
+  const int d = a.d, tw = d / EPC, teams = kThreads / tw;   // threads of a team; teams
+  const int team = (int)threadIdx.x / tw, e = (int)threadIdx.x % tw * EPC;
+  const int64_t t = a.pos[b];
   uint8_t* seq = a.arena + (size_t)b * a.stride;
   const size_t grp = (size_t)j * a.hkv + g;
   T* Kw = reinterpret_cast<T*>(seq + a.kw) + grp * a.Wx * d;
   T* Vw = reinterpret_cast<T*>(seq + a.vw) + grp * a.Wx * d;
-  float* ps = reinterpret_cast<float*>(seq + a.ps) + (grp * 2 + bank) * 2 * d;   // K sums, V sums
-  const T* Kn = static_cast<const T*>(a.K_new);
-  const T* Vn = static_cast<const T*>(a.V_new);
-  const int64_t c0 = t / S, c1 = (t + n - 1) / S;
-  const int64_t cfirst = c0 > c1 - a.P + 1 ? c0 : c1 - a.P + 1;
-  float sk = 0.f, sv = 0.f;
-  for (int64_t c = cfirst; c <= c1; ++c) {
-    const int64_t r0 = t > c * S ? t : c * S, r1 = t + n < (c + 1) * S ? t + n : (c + 1) * S;
-    const bool carry = c == c0 && t % S != 0;   // the chunk was opened by an earlier update
-    sk = carry ? ps[e] : 0.f;
-    sv = carry ? ps[d + e] : 0.f;
-    for (int64_t p = r0; p < r1; ++p) {
-      const size_t src = ((((size_t)b * a.max_new + (size_t)(p - t)) * a.D + j) * a.hkv + g) * d + e;
-      sk += Elem<T>::load(Kn + src);
-      sv += Elem<T>::load(Vn + src);
+  const size_t rstride = (size_t)a.D * a.hkv * d;
+  const size_t base = (size_t)b * a.max_new * rstride + grp * d + e;
+  const T* Kn = static_cast<const T*>(a.K_new) + base;
+  const T* Vn = static_cast<const T*>(a.V_new) + base;
+  // runs of `teams` chunks, the bank with the longer chunks first, dealt out to
+  // the zc workgroups in turn
+  int run = z;
+  for (int k = 0; k < 2; ++k) {
+    const int bank = (a.S0 >= a.S1) == (k == 0) ? 0 : 1;
+    const int S = bank ? a.S1 : a.S0;
+    const int64_t c0 = div_pos(t, S), c1 = div_pos(t + n - 1, S);
+    const int64_t cfirst = c0 > c1 - a.P + 1 ? c0 : c1 - a.P + 1;
+    const int items = (int)(c1 - cfirst) + 1, runs = (items + teams - 1) / teams;
+    float* ps = reinterpret_cast<float*>(seq + a.ps) + (grp * 2 + bank) * 2 * d + e;   // K, V sums
+    for (; run < runs; run += a.zc) {
+      // items: the first chunk, the last, then the ones between
+      const int item = run * teams + team;
+      const int64_t c = item == 0 ? cfirst : item == 1 ? c1 : cfirst + item - 1;
+      const bool live = item < items;
+      float sk[EPC], sv[EPC];
+      if (live) {
+        const int64_t r0 = t > c * S ? t : c * S, r1 = t + n < (c + 1) * S ? t + n : (c + 1) * S;
+        const bool carry = c == c0 && c0 * S != t;   // the chunk was opened by an earlier update
+        const int f0 = (int)(r0 - t), f1 = (int)(r1 - t);
+#pragma unroll
+        for (int i = 0; i < EPC; ++i) { sk[i] = carry ? ps[i] : 0.f; sv[i] = carry ? ps[d + i] : 0.f; }
+        for (int p0 = f0; p0 < f1; p0 += U) {
+          u32x4 kx[U], vx[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {   // rows past the chunk repeat its last one (not added)
+            const size_t row = (size_t)min(p0 + u, f1 - 1) * rstride;
+            kx[u] = *reinterpret_cast<const u32x4*>(Kn + row);
+            vx[u] = *reinterpret_cast<const u32x4*>(Vn + row);
+          }
+          __builtin_amdgcn_sched_barrier(0);   // all loads of the round are in flight
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const bool in = p0 + u < f1;
+            const T* kp = reinterpret_cast<const T*>(&kx[u]);
+            const T* vp = reinterpret_cast<const T*>(&vx[u]);
+#pragma unroll
+            for (int i = 0; i < EPC; ++i) {
+              const float nk = sk[i] + Elem<T>::load(kp + i), nv = sv[i] + Elem<T>::load(vp + i);
+              sk[i] = in ? nk : sk[i];
+              sv[i] = in ? nv : sv[i];
+            }
+          }
+        }
+        const float cnt = (float)(r1 - c * S);
+        const int slot = a.Wr + bank * a.P + mod_pos(c, a.P);
+        uint4 ko, vo;
+        T* kq = reinterpret_cast<T*>(&ko);
+        T* vq = reinterpret_cast<T*>(&vo);
+#pragma unroll
+        for (int i = 0; i < EPC; ++i) {
+          Elem<T>::store(kq + i, sk[i] / cnt);
+          Elem<T>::store(vq + i, sv[i] / cnt);
+        }
+        *reinterpret_cast<uint4*>(Kw + (size_t)slot * d + e) = ko;
+        *reinterpret_cast<uint4*>(&Vs[team * d + e]) = vo;
+        if (e == 0) slots[team] = slot;
+      } else if (e == 0) {
+        slots[team] = -1;
+      }
+      __syncthreads();
+      if (live && c == c1) {   // the last chunk's sums (used next time only if it is still open)
+#pragma unroll
+        for (int i = 0; i < EPC; ++i) { ps[i] = sk[i]; ps[d + i] = sv[i]; }
+      }
+      for (int i = threadIdx.x; i < teams * d; i += kThreads) {   // lanes take the run's slots
+        const int slot = slots[i % teams];
+        if (slot >= 0) Vw[(size_t)(i / teams) * a.Wx + slot] = Vs[(i % teams) * d + i / teams];
+      }
+      __syncthreads();
     }
-    const float cnt = (float)(r1 - c * S);
-    const int slot = a.Wr + bank * a.P + (int)(c % a.P);
-    Elem<T>::store(Kw + (size_t)slot * d + e, sk / cnt);
-    Elem<T>::store(Vw + (size_t)e * a.Wx + slot, sv / cnt);
+    run -= runs;
   }
-  ps[e] = sk;   // the last chunk's sums (used next time only if it is still open)
-  ps[d + e] = sv;
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) views_pool_kernel(PoolArgs a) {
+__global__ void __launch_bounds__(kThreads) views_pool_kernel(PoolArgs a) {
   views_pool_body<T>(a);
-  commit_tail(a.ct);
+  commit_tail(a.ct, blockIdx.z / a.zc);
 }
 
 __global__ void views_commit_kernel(int batch, int64_t* pos, const int32_t* n_new,
@@ -510,6 +797,16 @@ __global__ void views_commit_kernel(int batch, int64_t* pos, const int32_t* n_ne
     atomicOr(status, kFlagRange);
   else
     pos[b] += n;
+}
+
+constexpr int kMaxSplits = 32;   // row ranges of one (group, layer, sequence)
+
+// Compute waves of the bf16 kernel for this shape; 0: the vector kernel.
+int views_rows_waves(const Shape& s) {
+  if (s.dtype != LDR_BF16 || (s.d != 64 && s.d != 128)) return 0;
+  if (!s.learned) return 4;   // ring writes and boundary only
+  const int q = s.rep * s.R;
+  return q == 32 || q == 64 || q == 128 ? q / 16 : 0;
 }
 
 template <typename T>
@@ -525,7 +822,42 @@ hipError_t launch_update_t(const UpdateArgs& a, int dpt, dim3 grid, hipStream_t 
   return hipGetLastError();
 }
 
+// The bf16 kernel for NB stages; NW = 4 waves where there are no summary queries.
+template <int NB, bool SUM>
+hipError_t launch_rows(const Shape& s, const UpdateArgs& a, dim3 grid, hipStream_t st) {
+#define LDR_VU(DH, NW)                                                                        \
+  if (s.d == DH && views_rows_waves(s) == NW) {                                               \
+    hipLaunchKernelGGL((views_rows_kernel<DH, NW, NB, SUM>), grid, dim3((NB > 1 ? NW + 1 : NW) * 64), \
+                       0, st, a);                                                             \
+    return hipGetLastError();                                                                 \
+  }
+  LDR_VU(128, 4) LDR_VU(64, 4)
+  if constexpr (SUM) { LDR_VU(128, 2) LDR_VU(128, 8) LDR_VU(64, 2) LDR_VU(64, 8) }
+#undef LDR_VU
+  return hipErrorInvalidValue;
+}
+
 }  // namespace
+
+// Row ranges of an update with a learned summary: as many as keep the launch
+// within the two workgroups per CU that are resident at once (a 4096-row chunk
+// of one Qwen3-8B sequence, 40 units: 6 ranges 44.6 us with the merge, 10 41.1,
+// 13 -- 520 workgroups, a second round -- 47.8), each of at least 4 tiles (128
+// rows; shorter ranges only add partials to write and merge). 1: no split.
+int views_splits(const Shape& s, int batch, int max_new) {
+  const long units = (long)s.hkv * s.D * batch;
+  long sp = 512 / units;
+  sp = sp < kMaxSplits ? sp : kMaxSplits;
+  const long by_rows = max_new / (4 * kTileRows);
+  sp = sp < by_rows ? sp : by_rows;
+  return sp > 1 ? (int)sp : 1;
+}
+
+size_t views_scratch_bytes(const Shape& s, int batch) {
+  if (!s.learned || !views_rows_waves(s)) return 0;
+  const int sp = views_splits(s, batch, 0x7fffffff);
+  return sp > 1 ? (size_t)s.hkv * s.D * batch * sp * s.rep * s.R * (s.d + 2) * sizeof(float) : 0;
+}
 
 // Threads per summary query: Q = rep * R queries share 256 threads.
 int views_dims_per_thread(const Shape& s) {
@@ -553,7 +885,7 @@ hipError_t launch_views_update(const Shape& s, const Layout& L, int batch, void*
                                int64_t* pos, const void* G, const int32_t* n_new,
                                int max_new, const void* K_new, const void* V_new,
                                const void* h_new, hipStream_t st, int32_t* status,
-                               int32_t* done) {
+                               int32_t* done, void* scratch) {
   UpdateArgs a;
   a.arena = static_cast<uint8_t*>(arena); a.stride = L.stride;
   a.kw = L.kw; a.vw = L.vw; a.m = L.m; a.eta = L.eta; a.h = L.h;
@@ -565,18 +897,34 @@ hipError_t launch_views_update(const Shape& s, const Layout& L, int batch, void*
   a.Wx = s.Wx;
   a.inv_sqrt_d = 1.0f / sqrtf((float)s.d);
   const dim3 grid(s.hkv, s.D, batch);
-  a.ct = CommitTail{done, (int)(grid.x * grid.y * grid.z), pos, n_new,
-                    max_new, batch, status};
+  a.splits = 1; a.part = nullptr; a.part_ml = nullptr;
+  a.ct = CommitTail{done, (int)(grid.x * grid.y), pos, n_new, max_new, status};
   const int q = s.rep * s.R;
-  if (s.dtype == LDR_BF16 && (s.d == 64 || s.d == 128) && q % 16 == 0) {
-    const int nw = q / 16;
-#define LDR_VU(DH, NW) \
-  if (s.d == DH && nw == NW) { \
-    hipLaunchKernelGGL((views_update_mfma_kernel<DH, NW>), grid, dim3(NW * 64), 0, st, a); \
-    return hipGetLastError(); \
-  }
-    LDR_VU(128, 4) LDR_VU(128, 2) LDR_VU(128, 8) LDR_VU(64, 4) LDR_VU(64, 2) LDR_VU(64, 8)
-#undef LDR_VU
+  const bool rows_kernel = views_rows_waves(s) > 0;
+  if (rows_kernel && s.learned && max_new <= kTileRows) {
+    return launch_rows<1, true>(s, a, grid, st);
+  } else if (rows_kernel && s.learned) {
+    const int sp = scratch ? views_splits(s, batch, max_new) : 1;
+    const dim3 sgrid(s.hkv, s.D, batch * sp);
+    a.splits = sp;
+    if (sp == 1) {
+      return launch_rows<4, true>(s, a, grid, st);
+    } else {
+      const size_t rows = (size_t)s.hkv * s.D * batch * sp * q;
+      a.part = static_cast<float*>(scratch); a.part_ml = a.part + rows * s.d;
+      const CommitTail ct = a.ct;
+      a.ct.done = nullptr;   // the merge commits
+      hipError_t e = launch_rows<4, true>(s, a, sgrid, st);
+      if (e != hipSuccess) return e;
+      a.ct = ct;
+      const dim3 mgrid(s.hkv * s.D, q / (1024 / s.d), batch);
+      if (s.d == 128) hipLaunchKernelGGL(views_merge_kernel<128>, mgrid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL(views_merge_kernel<64>, mgrid, dim3(256), 0, st, a);
+      return hipGetLastError();
+    }
+  } else if (rows_kernel) {
+    return max_new <= kTileRows ? launch_rows<1, false>(s, a, grid, st)
+                                : launch_rows<4, false>(s, a, grid, st);
   }
   const int dpt = views_dims_per_thread(s);
   return s.dtype == LDR_BF16 ? launch_update_t<uint16_t>(a, dpt, grid, st)
@@ -592,9 +940,17 @@ hipError_t launch_views_pool(const Shape& s, const Layout& L, int batch, void* a
   a.ps = L.ps; a.pos = pos; a.n_new = n_new; a.max_new = max_new; a.K_new = K_new;
   a.V_new = V_new; a.D = s.D; a.hkv = s.hkv; a.d = s.d; a.Wr = s.Wr; a.Wx = s.Wx; a.P = s.P;
   a.S0 = s.S0; a.S1 = s.S1;
-  const dim3 grid(s.hkv, s.D, batch), block(2 * s.d);   // d <= 128
-  a.ct = CommitTail{done, (int)(grid.x * grid.y * grid.z), pos, n_new,
-                    max_new, batch, status};
+  // workgroups per (group, layer, sequence): one per run of chunks the rows can
+  // touch, at most about 8 workgroups per CU in all
+  const int teams = kThreads / (s.d * (int)s.el / 16);
+  const int c0 = max_new / s.S0 + 1, c1 = max_new / s.S1 + 1;
+  const long runs = ((c0 < s.P ? c0 : s.P) + teams - 1) / teams +
+                    ((c1 < s.P ? c1 : s.P) + teams - 1) / teams;
+  const long cap = 2048 / ((long)s.hkv * s.D * batch);
+  const long zc = runs < cap ? runs : cap;
+  a.zc = zc > 1 ? (int)zc : 1;
+  const dim3 grid(s.hkv, s.D, batch * a.zc), block(kThreads);
+  a.ct = CommitTail{done, (int)(grid.x * grid.y) * a.zc, pos, n_new, max_new, status};
   if (s.dtype == LDR_BF16)
     hipLaunchKernelGGL(views_pool_kernel<uint16_t>, grid, block, 0, st, a);
   else

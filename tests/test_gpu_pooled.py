@@ -95,3 +95,16 @@ def test_pooled_full_size_qwen3_8b(gpu_lib):
         err, cos = row_errors(zc[b], ref)
         assert err.max() <= 2e-2, err.max()
         assert cos.min() >= 0.999, cos.min()
+
+
+@pytest.mark.parametrize("batch,strides", [(1, (4, 16)), (2, (16, 4)), (40, (3, 64))])
+def test_pooled_chunks_shared_by_teams(gpu_lib, batch, strides):
+    """Chunks of one update dealt out over several workgroups (few sequences)
+    or one (many): open first chunks, updates inside one chunk, banks that wrap
+    within an update, in either order of the strides."""
+    s = MINI_BF16_POOLED.replace(pool_strides=strides)
+    p = Pair(gpu_lib, s, batch, None, oracle_seqs=sorted({0, batch - 1}))
+    for i, n in enumerate((5, 1, 700, 2, 130, 1030)):
+        K, V, h = synth.decode_rows(s, batch, n, i, device="cuda")
+        p.ingest([max(0, n - b % 3) for b in range(batch)], K, V, h)
+        check_views(p)

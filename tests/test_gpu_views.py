@@ -68,6 +68,49 @@ def test_out_of_range_count_sets_sticky_flag(gpu_lib):
     assert p.views.status() == gpu_lib.LDR_OK
 
 
+# query tiles of 2, 4 and 8 waves at both head widths; rows around the edges of
+# a 32-row tile and of the window, row ranges over several workgroups (one or
+# two sequences: 256 rows split in two, 1000 in seven or so), ragged and empty
+# counts, every update continuing from the one before
+@pytest.mark.parametrize("hq,d,drop", [(8, 128, 0), (4, 128, 0), (16, 64, 0), (8, 64, 0),
+                                       (8, 128, 1), (8, 128, 2), (8, 64, 6)])
+def test_row_tiles_and_ranges(gpu_lib, hq, d, drop):
+    s = MINI_BF16.replace(n_q_heads=hq, head_dim=d, drop_views=drop)
+    p = Pair(gpu_lib, s, 2, None if drop & 2 else synth.make_G(s, device="cuda"))
+    for i, (a, b) in enumerate([(1, 0), (31, 33), (32, 1), (0, 65), (255, 256), (1000, 129),
+                                (97, 1000), (17, 3)]):
+        K, V, h = synth.decode_rows(s, 2, max(a, b) + (i & 1), i, device="cuda")
+        p.ingest([a, b], K, V, h)
+        # P enters as two bf16 terms, within 2^-17 of itself: |dM| <= 2^-17
+        # sum p |v|, and a weighted mean of |v| over N(0, 1) rows stays below
+        # the largest |M| or 1
+        check_views(p, atol_m=2.0 ** -17)
+    assert p.views.status() == 0
+
+
+def test_infinite_value_and_nan_key(gpu_lib):
+    """An infinite value in the last, ragged tile leaves the summary of its
+    group's heads not finite in that dimension only (infinite, or NaN where the
+    two bf16 terms of its probability differ in sign; padding rows add
+    nothing), a NaN key makes the summary of its group's heads NaN and leaves
+    the others alone; split and unsplit rows."""
+    s = MINI_BF16
+    for rows in (20, 300):
+        v = gpu_lib.Views(s, 1, synth.make_G(s, device="cuda")).init()
+        K, V, h = synth.decode_rows(s, 1, rows, 3, device="cuda")
+        V[0, rows - 1, 0, 0, 5] = float("inf")
+        K[0, rows - 2, 1, 1, 7] = float("nan")
+        v.update(torch.tensor([rows], dtype=torch.int32, device="cuda"), K, V, h)
+        M, eta = (x[0].cpu() for x in v.summary())
+        rep = s.n_q_heads // s.n_kv_heads
+        fin = torch.isfinite(M[0])
+        assert not fin[:rep, :, 5].any()
+        fin[:rep, :, 5] = True
+        assert fin.all() and torch.isfinite(eta[0]).all()
+        assert torch.isnan(M[1, rep:]).all() and torch.isnan(eta[1, rep:]).all()
+        assert torch.isfinite(M[1, :rep]).all() and torch.isfinite(eta[1, :rep]).all()
+
+
 @pytest.mark.slow
 def test_full_size_qwen3_8b_prefill_sampled(gpu_lib):
     """Qwen3-8B shape, batch 16, prefix 32768 ingested in 4096-row chunks, then
