@@ -27,6 +27,7 @@
 // contraction, correctly rounded division), so every key fl(x + g) is
 // reproducible bit for bit.
 #include <mutex>
+#include <type_traits>
 
 #include "ldr_internal.h"
 #include "noise.h"
@@ -68,10 +69,7 @@ constexpr uint32_t kChunkStream = 3;
 // 8-bit digits, most significant first, LDS histograms), then the index cut
 // among the tokens equal to it. One workgroup per row.
 constexpr int kSelThreads = 1024;
-__global__ void __launch_bounds__(kSelThreads) topk_select_kernel(const float* logits, int vocab,
-                                                                  int k, TopK* sel, int row_mul,
-                                                                  int row_add) {
-  const float* z = logits + ((long)blockIdx.x * row_mul + row_add) * vocab;
+__device__ TopK radix_select(const float* z, int vocab, int k) {
   __shared__ uint32_t hist[256];
   __shared__ uint32_t s_digit, s_above;
   __shared__ int wcount[kSelThreads / 64];
@@ -129,7 +127,210 @@ __global__ void __launch_bounds__(kSelThreads) topk_select_kernel(const float* l
     }
     v_cut = s_cut;
   }
-  if (threadIdx.x == 0) sel[blockIdx.x] = TopK{prefix, v_cut};
+  return TopK{prefix, v_cut};
+}
+
+__global__ void __launch_bounds__(kSelThreads) topk_select_kernel(const float* logits, int vocab,
+                                                                  int k, TopK* sel, int row_mul,
+                                                                  int row_add) {
+  const TopK t =
+      radix_select(logits + ((long)blockIdx.x * row_mul + row_add) * vocab, vocab, k);
+  if (threadIdx.x == 0) sel[blockIdx.x] = t;
+}
+
+// Log-mass of the support tokens of a chunk, whose 16 tokens sit 4 each on 4
+// consecutive lanes (x: the lane's, at v; tokens at or past v1 are outside), in
+// the balanced pairwise order; every lane returns it.
+template <bool UNIT_T, bool TOPK>
+__device__ inline float chunk_mass(const TopK& sel, const float (&x)[4], int v, int v1, float T) {
+  float zt[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    bool in = v + i < v1;
+    if constexpr (TOPK) in = in && in_support(sel, x[i], v + i);
+    zt[i] = in ? (UNIT_T ? x[i] : x[i] / T) : -INFINITY;  // IEEE division
+  }
+  float m = fmaxf(fmaxf(zt[0], zt[1]), fmaxf(zt[2], zt[3]));
+  m = fmaxf(m, dpp<0xB1>(m));   // the chunk's 4 lanes
+  m = fmaxf(m, dpp<0x4E>(m));
+  float e[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) e[i] = chunk_term(zt[i], m);
+  float sum = (e[0] + e[1]) + (e[2] + e[3]);
+  sum += dpp<0xB1>(sum);
+  sum += dpp<0x4E>(sum);
+  return chunk_log_mass(m, sum);
+}
+__device__ inline float support_chunk_mass(const TopK& sel, const float (&x)[4], int v, int v1,
+                                           float T) {
+  return T == 1.f ? chunk_mass<true, true>(sel, x, v, v1, T)
+                  : chunk_mass<false, true>(sel, x, v, v1, T);
+}
+
+// The top-k support of a row and its chunk log-masses in one launch, one
+// workgroup per row, for k <= kSelMaxK and at most kSelMaxChunks chunks:
+//  1. one pass over the row keeps every 16-token chunk's largest order_key in
+//     LDS (16-byte loads, four sweeps in flight per lane);
+//  2. a value t0 such that at least k chunks reach it, by bitwise search over
+//     those maxima: at least k tokens reach t0, so the support lies in the
+//     chunks that do, and the search stops once they are few;
+//  3. the exact k-th largest key among those chunks' tokens, held in registers,
+//     and the index cut among its equals, by the same bitwise search;
+//  4. the log-masses of those chunks (the operations of chunk_lse_kernel, so the
+//     same bits); every other chunk has no support token and takes -inf, so the
+//     log-mass pass over the logits is not needed.
+// Where ties put more than kSelCap chunks at t0, the row falls back to the radix
+// selection and a pass for the log-masses. The radix kernel reads the row five
+// times with 4-byte loads and one LDS atomic per token, most of them on a few
+// bins. 256 rows of 151936, k = 50: 244 us and 29 us for the log-mass pass then,
+// 49 us for this launch (3.2 TB/s; half of it the pass over the row).
+// Beyond k = 256 the candidate chunks outgrow the registers; the radix kernel
+// stays for those.
+constexpr int kSelMaxK = 256, kSelMaxChunks = 14336, kSelCap = 512;
+
+template <bool VEC>
+__global__ void __launch_bounds__(kSelThreads) topk_chunks_kernel(SampleArgs a, int k, TopK* sel) {
+  constexpr int KPT = kSelMaxChunks / kSelThreads, EPT = kSelCap * kChunk / kSelThreads;
+  extern __shared__ uint32_t mx[];   // [nch] chunk maxima, then the candidate chunks
+  __shared__ int cnt[3], s_nc;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int r = blockIdx.x, V = a.vocab, nch = a.nch;
+  const float* z = a.logits + ((long)r * a.row_mul + a.row_add) * V;
+  float* L = a.L ? a.L + (long)r * a.ldL : nullptr;
+  int* cand = reinterpret_cast<int*>(mx + nch);
+  if (tid < 3) cnt[tid] = 0;
+  if (tid == 3) s_nc = 0;
+
+  {  // 1. chunk maxima: 4 lanes hold a chunk, 4 tokens each
+    constexpr int U = 4, kSweep = kSelThreads * 4;
+    auto load = [&](int v, float (&x)[4]) {
+      if (VEC && v + 4 <= V) {
+        const float4 t = *reinterpret_cast<const float4*>(z + v);
+        x[0] = t.x; x[1] = t.y; x[2] = t.z; x[3] = t.w;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = z[min(v + i, V - 1)];   // repeats: the same maximum
+      }
+    };
+    for (int vb = 4 * tid; vb < (V + 15) / 16 * 16; vb += U * kSweep) {
+      float x[U][4];
+#pragma unroll
+      for (int u = 0; u < U; ++u) load(min(vb + u * kSweep, (V - 1) / 4 * 4), x[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int v = vb + u * kSweep;
+        uint32_t m = max(max(order_key(x[u][0]), order_key(x[u][1])),
+                         max(order_key(x[u][2]), order_key(x[u][3])));
+        if (v >= V) m = 0u;   // lanes of the last chunk past the row
+        m = max(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0xB1, 0xF, 0xF, false));
+        m = max(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x4E, 0xF, 0xF, false));
+        if ((tid & 3) == 0 && v < V) mx[v / kChunk] = m;
+      }
+    }
+  }
+  __syncthreads();
+  uint32_t key[KPT];
+#pragma unroll
+  for (int i = 0; i < KPT; ++i) {
+    const int c = tid + i * kSelThreads;
+    key[i] = c < nch ? mx[c] : 0u;
+  }
+  // workgroup-wide count of pred over N values a thread; uniform, one barrier
+  int turn = 0;
+  auto count = [&](auto n_tag, auto&& pred) -> int {
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < decltype(n_tag)::value; ++i) c += __popcll(__ballot(pred(i)));
+    if (tid == 0) cnt[turn == 2 ? 0 : turn + 1] = 0;
+    if (lane == 0 && c) atomicAdd(&cnt[turn], c);
+    __syncthreads();
+    c = cnt[turn];
+    turn = turn == 2 ? 0 : turn + 1;
+    return c;
+  };
+  using NK = std::integral_constant<int, KPT>;
+  using NE = std::integral_constant<int, EPT>;
+
+  // 2. t0: chunks with a maximum >= t0 hold the support
+  uint32_t t0 = 0u;
+  int nc = nch;
+  const int enough = 64 + 2 * k < kSelCap ? 64 + 2 * k : kSelCap;
+  for (int bit = 31; bit >= 0 && nc > enough; --bit) {
+    const uint32_t t = t0 | (1u << bit);
+    const int c = count(NK{}, [&](int i) { return key[i] >= t; });
+    if (c >= k) { t0 = t; nc = c; }
+  }
+
+  if (nc > kSelCap) {   // ties: the general selection, then every chunk's log-mass
+    const TopK t = radix_select(z, V, k);
+    if (tid == 0) sel[r] = t;
+    if (L)
+      for (int vb = 4 * tid; vb < (V + 15) / 16 * 16; vb += 4 * kSelThreads) {
+        float x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = vb + i < V ? z[vb + i] : -INFINITY;
+        const float l = support_chunk_mass(t, x, vb, V, a.T);
+        if ((tid & 3) == 0) L[vb / kChunk] = l;
+      }
+    return;
+  }
+
+  // the candidate chunks, in any order; the others have no support token
+#pragma unroll
+  for (int i = 0; i < KPT; ++i) {
+    const int c = tid + i * kSelThreads;
+    const bool in = c < nch && key[i] >= t0;
+    const uint64_t m = __ballot(in);
+    int at = 0;
+    if (lane == 0 && m) at = atomicAdd(&s_nc, __popcll(m));
+    at = __shfl(at, 0);
+    if (in) cand[at + __popcll(m & ((1ull << lane) - 1ull))] = c;
+    else if (L && c < nch) L[c] = -INFINITY;
+  }
+  __syncthreads();
+
+  // 3. the k-th largest key of their tokens
+  uint32_t ek[EPT];
+  int ev[EPT];   // token, -1: none
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int e = tid + i * kSelThreads, ci = e / kChunk;
+    int v = -1;
+    if (ci < nc) v = cand[ci] * kChunk + (e & (kChunk - 1));
+    if (v >= V) v = -1;
+    ev[i] = v;
+    ek[i] = v >= 0 ? order_key(z[v]) : 0u;
+  }
+  uint32_t tau = 0u;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t t = tau | (1u << bit);
+    if (count(NE{}, [&](int i) { return ek[i] >= t; }) >= k) tau = t;
+  }
+  const int above = count(NE{}, [&](int i) { return ev[i] >= 0 && ek[i] > tau; });
+  const int equal = count(NE{}, [&](int i) { return ev[i] >= 0 && ek[i] == tau; });
+  // the lowest k - above of the equal tokens are inside
+  int v_cut = V;
+  if (k - above < equal) {
+    v_cut = 0;   // the largest index with fewer than k - above equal tokens before it
+    for (int bit = 30; bit >= 0; --bit) {
+      const int t = v_cut | (1 << bit);
+      if (t >= V) continue;
+      if (count(NE{}, [&](int i) { return ev[i] >= 0 && ek[i] == tau && ev[i] < t; }) < k - above)
+        v_cut = t;
+    }
+  }
+  const TopK t{tau, v_cut};
+  if (tid == 0) sel[r] = t;
+  // 4. log-masses of the candidate chunks
+  if (L)
+    for (int i = tid; i < nc * 4; i += kSelThreads) {
+      const int c = cand[i >> 2], v = c * kChunk + (i & 3) * 4;
+      float x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[q] = v + q < V ? z[v + q] : -INFINITY;
+      const float l = support_chunk_mass(t, x, v, V, a.T);
+      if ((i & 3) == 0) L[c] = l;
+    }
 }
 
 // The lane's G values of a sweep at v (G a multiple of 4): 16-byte loads
@@ -280,25 +481,9 @@ __global__ void __launch_bounds__(kThreads) chunk_lse_kernel(SampleArgs a, int v
   const TopK sel = TOPK ? a.sel[r] : TopK{0u, 0};
   const float T = a.T;
   const int t4 = 4 * (int)threadIdx.x;
-  // the chunk of the 4 tokens x at v (tokens at or past v1 are outside)
   auto chunk = [&](int v, const float (&x)[4]) {
-    float zt[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      bool in = v + i < v1;
-      if constexpr (TOPK) in = in && in_support(sel, x[i], v + i);
-      zt[i] = in ? (UNIT_T ? x[i] : x[i] / T) : -INFINITY;  // IEEE division
-    }
-    float m = fmaxf(fmaxf(zt[0], zt[1]), fmaxf(zt[2], zt[3]));
-    m = fmaxf(m, dpp<0xB1>(m));   // the chunk's 4 lanes
-    m = fmaxf(m, dpp<0x4E>(m));
-    float e[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) e[i] = chunk_term(zt[i], m);
-    float sum = (e[0] + e[1]) + (e[2] + e[3]);
-    sum += dpp<0xB1>(sum);
-    sum += dpp<0x4E>(sum);
-    if ((threadIdx.x & 3) == 0 && v < v1) L[v / kChunk] = chunk_log_mass(m, sum);
+    const float l = chunk_mass<UNIT_T, TOPK>(sel, x, v, v1, T);
+    if ((threadIdx.x & 3) == 0 && v < v1) L[v / kChunk] = l;
   };
   int vb = v0;
   for (; vb + U * kSweep <= v1; vb += U * kSweep) {
@@ -616,13 +801,6 @@ hipError_t noalloc_scratch(void** out) {
   return hipSuccess;
 }
 
-hipError_t launch_topk_select(const float* logits, int rows, int vocab, int k, TopK* sel,
-                              hipStream_t st) {
-  hipLaunchKernelGGL(topk_select_kernel, dim3(rows), dim3(kSelThreads), 0, st, logits, vocab, k,
-                     sel, 1, 0);
-  return hipGetLastError();
-}
-
 namespace {
 // Arguments of the sampler's kernels for `rows` rows, workspace ws (the
 // chunk log-masses, then the partials).
@@ -660,6 +838,25 @@ hipError_t chunk_lse(const SampleArgs& a, int v0, int v1, hipStream_t st) {
   return hipGetLastError();
 }
 
+bool topk_in_chunks(const SampleArgs& a, int k) {
+  return k <= kSelMaxK && a.nch <= kSelMaxChunks;
+}
+
+// The rows' top-k supports; with topk_in_chunks also their log-masses (a.L).
+hipError_t topk_support(const SampleArgs& a, int k, TopK* sel, hipStream_t st) {
+  if (!topk_in_chunks(a, k)) {
+    hipLaunchKernelGGL(topk_select_kernel, dim3(a.rows), dim3(kSelThreads), 0, st, a.logits,
+                       a.vocab, k, sel, a.row_mul, a.row_add);
+    return hipGetLastError();
+  }
+  const size_t lds = (size_t)(a.nch + kSelCap) * 4;   // within the 64 KB a kernel gets unasked
+  if (a.vec)
+    hipLaunchKernelGGL(topk_chunks_kernel<true>, dim3(a.rows), dim3(kSelThreads), lds, st, a, k, sel);
+  else
+    hipLaunchKernelGGL(topk_chunks_kernel<false>, dim3(a.rows), dim3(kSelThreads), lds, st, a, k, sel);
+  return hipGetLastError();
+}
+
 hipError_t sample_finish(const SampleArgs& a, int32_t* tokens, float* lse, float* logq,
                          hipStream_t st) {
   if (a.T > 0.f) {
@@ -675,6 +872,13 @@ hipError_t sample_finish(const SampleArgs& a, int32_t* tokens, float* lse, float
 }
 }  // namespace
 
+hipError_t launch_topk_select(const float* logits, int rows, int vocab, int k, TopK* sel,
+                              hipStream_t st) {
+  SampleArgs a = sample_args(logits, rows, vocab, 1.f, 0, 0, nullptr, 1, 0);
+  a.L = nullptr;   // the supports alone
+  return topk_support(a, k, sel, st);
+}
+
 hipError_t launch_sample(const float* logits, int rows, int vocab, float temperature,
                          int top_k, uint64_t seed, uint64_t step, int32_t* tokens, float* lse,
                          float* logq, void* ws, size_t sel_off, hipStream_t st, int row_mul,
@@ -683,11 +887,10 @@ hipError_t launch_sample(const float* logits, int rows, int vocab, float tempera
   if (temperature > 0.f) {
     if (top_k > 0 && top_k < vocab) {  // T = 0 is the argmax either way
       TopK* sel = reinterpret_cast<TopK*>(static_cast<uint8_t*>(ws) + sel_off);
-      hipLaunchKernelGGL(topk_select_kernel, dim3(rows), dim3(kSelThreads), 0, st, logits, vocab,
-                         top_k, sel, row_mul, row_add);
-      const hipError_t e = hipGetLastError();
+      const hipError_t e = topk_support(a, top_k, sel, st);   // with the log-masses, if it can
       if (e != hipSuccess) return e;
       a.sel = sel;
+      if (topk_in_chunks(a, top_k)) return sample_finish(a, tokens, lse, logq, st);
     }
     const hipError_t e = chunk_lse(a, 0, vocab, st);
     if (e != hipSuccess) return e;

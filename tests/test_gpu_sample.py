@@ -98,6 +98,22 @@ def test_top_k_tokens_exact(gpu_lib, rows, vocab, T, k):
         assert tok[r] in set(OS.support(z[r].cpu().numpy(), k).tolist())
 
 
+@pytest.mark.parametrize("rows,vocab,k", [(3, 151936, 256), (3, 151936, 257), (5, 5003, 255),
+                                          (4, 1001, 200), (2, 17, 16), (2, 229376, 20),
+                                          (2, 229377, 20), (300, 4097, 30)])
+def test_top_k_by_chunk_maxima(gpu_lib, rows, vocab, k):
+    """Both sides of the limits of the selection by chunk maxima (k = 256,
+    14336 chunks), fewer chunks than k, rows off 16 bytes, one chunk more than
+    a sweep; a row whose largest logits share a few chunks, one with -inf
+    beyond its first tokens and one with equal logits in every chunk."""
+    z = _logits(rows, vocab, rows + vocab + k)
+    z[0, :min(vocab, 3 * 16)] += 20.0
+    z[1, max(k // 2, 1):] = -float("inf")
+    if rows > 2:
+        z[2, ::16] = 9.0
+    _check_sample(gpu_lib, z, 0.8, k, seed=k, step=2)
+
+
 def test_top_k_ties_at_the_boundary(gpu_lib):
     # few distinct values: the k-th value is shared by many tokens, and the
     # lowest indices among them are inside
