@@ -94,8 +94,8 @@ static WsPlan plan_ws(const Shape& s, int batch) {
   w.gu = plan_gemm(s.dtype, M, 2 * s.mlp, s.hidden, false, true);   // SwiGLU epilogue: no split
   // the down projection reads the SwiGLU rows in the fragment layout when the
   // SwiGLU GEMM (itself on the fragment layout) can write them so
-  w.down = plan_gemm(s.dtype, M, s.hidden, s.mlp, true, false, gemm_plan_frag(w.gu));
-  w.lm = plan_gemm(s.dtype, M, s.vocab, s.hidden, false);     // writes the logits directly
+  w.down = plan_gemm(s.dtype, M, s.hidden, s.mlp, true, false, w.gu.frag);
+  w.lm = plan_gemm(s.dtype, M, s.vocab, s.hidden, false, false, true);   // writes the logits directly
   size_t part = (size_t)w.fc.splits * batch * s.hidden;
   part = part > (size_t)w.qkv.splits * M * s.qkv_out ? part : (size_t)w.qkv.splits * M * s.qkv_out;
   part = part > (size_t)w.wo.splits * M * s.hidden ? part : (size_t)w.wo.splits * M * s.hidden;
@@ -115,7 +115,7 @@ static WsPlan plan_ws(const Shape& s, int batch) {
   w.nrmt = off; off = align_up(off + (s.dtype == LDR_BF16 ? tiled_elems(M, s.hidden) * 2 : 0));
   // the QKV and SwiGLU GEMMs' rows in the fragment layout (rows padded to 16)
   w.nrmf = off;
-  off = align_up(off + (gemm_plan_frag(w.gu) || gemm_plan_frag(w.qkv)
+  off = align_up(off + (w.gu.frag || w.qkv.frag || w.lm.frag
                             ? (size_t)(M + 15) / 16 * 16 * s.hidden * 2 : 0));
   w.bytes = off;
   return w;
@@ -413,10 +413,10 @@ static int draft_step_impl(const ldr_views* v, const ldr_weights* w, const int32
         break;
       case LDR_LAUNCH_SLOT_INIT:
         e = launch_slot_init(s, batch, p, ws.fc.splits, w, anchor, st,
-                             gemm_plan_frag(ws.qkv) ? base + ws.nrmf : nullptr);
+                             ws.qkv.frag ? base + ws.nrmf : nullptr);
         break;
       case LDR_LAUNCH_QKV_GEMM:
-        g.A = gemm_plan_frag(ws.qkv) ? static_cast<const void*>(base + ws.nrmf) : p.nrm;
+        g.A = ws.qkv.frag ? static_cast<const void*>(base + ws.nrmf) : p.nrm;
         g.lda = s.hidden; g.W = L.wqkv; g.ldw = s.hidden; g.out = p.part;
         g.ldo = s.qkv_out; g.split_stride = (long)M * s.qkv_out; g.M = M; g.N = s.qkv_out;
         g.K = s.hidden; g.splits = ws.qkv.splits;
@@ -426,7 +426,7 @@ static int draft_step_impl(const ldr_views* v, const ldr_weights* w, const int32
         e = launch_qkv_finish(s, M, p, ws.qkv.splits, &L, st);
         break;
       case LDR_LAUNCH_ATTENTION:
-        e = launch_attention(s, v->L, batch, p, j, &L, ws.qkv.splits, st, gemm_plan_frag(ws.wo));
+        e = launch_attention(s, v->L, batch, p, j, &L, ws.qkv.splits, st, ws.wo.frag);
         break;
       case LDR_LAUNCH_O_GEMM:
         g.A = p.o; g.lda = (long)s.hq * s.d; g.W = L.wo; g.ldw = (long)s.hq * s.d;
@@ -435,16 +435,16 @@ static int draft_step_impl(const ldr_views* v, const ldr_weights* w, const int32
         e = launch_gemm(s.dtype, EPI_STORE, ws.wo, g, st);
         break;
       case LDR_LAUNCH_POST_NORM:
-        e = gemm_plan_frag(ws.gu)
+        e = ws.gu.frag
                 ? launch_resid_norm(s, M, p, ws.wo.splits, L.post_norm, st, base + ws.nrmf,
                                     NRM_FRAG)
                 : launch_resid_norm(s, M, p, ws.wo.splits, L.post_norm, st);
         break;
       case LDR_LAUNCH_GATE_UP_GEMM:
-        g.A = gemm_plan_frag(ws.gu) ? static_cast<const void*>(base + ws.nrmf) : p.nrm;
+        g.A = ws.gu.frag ? static_cast<const void*>(base + ws.nrmf) : p.nrm;
         g.lda = s.hidden; g.W = L.w_gate_up; g.ldw = s.hidden; g.out = p.act;
         g.ldo = s.mlp; g.split_stride = 0; g.M = M; g.N = 2 * s.mlp; g.K = s.hidden;
-        g.splits = 1; g.mlp = s.mlp; g.out_frag = gemm_plan_frag(ws.down);
+        g.splits = 1; g.mlp = s.mlp; g.out_frag = ws.down.frag;
         e = launch_gemm(s.dtype, EPI_SWIGLU, ws.gu, g, st);
         break;
       case LDR_LAUNCH_DOWN_GEMM:
@@ -455,13 +455,14 @@ static int draft_step_impl(const ldr_views* v, const ldr_weights* w, const int32
         break;
       case LDR_LAUNCH_NEXT_NORM:
         if (j + 1 < s.D)   // the next layer's QKV input
-          e = gemm_plan_frag(ws.qkv)
+          e = ws.qkv.frag
                   ? launch_resid_norm(s, M, p, ws.down.splits, w->layers[j + 1].in_norm, st,
                                       base + ws.nrmf, NRM_FRAG)
                   : launch_resid_norm(s, M, p, ws.down.splits, w->layers[j + 1].in_norm, st);
         else               // the vocabulary head's input
           e = launch_resid_norm(s, M, p, ws.down.splits, w->final_norm, st,
-                                tiled_head ? base + ws.nrmt : nullptr);
+                                tiled_head ? base + ws.nrmt : ws.lm.frag ? base + ws.nrmf : nullptr,
+                                tiled_head ? NRM_TILED : NRM_FRAG);
         break;
       case LDR_LAUNCH_LM_HEAD:
         g.lda = s.hidden; g.ldw = s.hidden; g.out = logits; g.ldo = s.vocab;
@@ -480,7 +481,8 @@ static int draft_step_impl(const ldr_views* v, const ldr_weights* w, const int32
           g.A = base + ws.nrmt; g.W = w->lm_head_tiled;
           e = launch_gemm_tiled(g, st);
         } else {
-          g.A = p.nrm; g.W = w->lm_head;
+          g.A = ws.lm.frag ? static_cast<const void*>(base + ws.nrmf) : p.nrm;
+          g.W = w->lm_head;
           e = launch_gemm(s.dtype, EPI_LOGITS, ws.lm, g, st);
         }
         break;

@@ -2,21 +2,12 @@
 // fp32 accumulation, for the boundary fusion, the QKV / O / gate-up / down
 // projections of every layer and the vocabulary head (Sec. 2.3, App. B.1).
 //
-// With M = batch x B rows (256 at batch 16) these GEMMs stream each weight
-// once from HBM and reuse it across all M rows:
-//  * a workgroup owns a BM x BN output tile (BM = all M rows up to 256) and a
-//    1/splits share of K, with WM x WN waves of MTW x NTW 16x16 MFMA tiles;
-//  * both operands reach LDS through coalesced 16-byte loads (8 lanes per
-//    128-byte row segment), double-buffered, in 128-byte rows whose 16-byte
-//    chunks are XOR-swizzled (lds_chunk) so that both the stores and the
-//    16-lane fragment reads of v_mfma_f32_16x16x32_bf16 are conflict-free;
-//  * weight loads run WPF steps ahead and activation loads 2 steps ahead in
-//    register rings, so HBM latency is covered by several steps of MFMAs;
-//  * the loop body has no branches (rows past M or N load a clamped valid
-//    row whose results are never stored, prefetches past the last step reload
-//    it) and the per-step barrier waits for LDS traffic only, so prefetches
-//    stay in flight across it.
-// fp32: a plain SIMT tile kernel with the same epilogues.
+// These GEMMs stream each weight once from HBM and reuse it across all M =
+// batch x B rows: loader waves stage the weights through LDS by DMA while
+// compute waves read the activation rows straight into MFMA fragments
+// (frag_gemm below, tiles of 16 to 256 rows); the vocabulary head above 64 rows
+// has a kernel of its own (gemm_tiled_kernel). fp32: a plain SIMT tile kernel
+// with the same epilogues.
 //
 // Epilogues: EPI_STORE writes fp32 (split-K partials); EPI_LOGITS writes the
 // fp32 logits; EPI_SWIGLU reads the gate and up rows of w_gate_up interleaved
@@ -38,15 +29,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // memcpys that keep arrays of them in scratch).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int BK = 64;        // K step: one LDS stage, two MFMA k-steps
-constexpr int LDK = BK;       // LDS row (elements): 128 B, 16-byte chunks swizzled
-// Physical 16-byte chunk of logical chunk c (0..7) in LDS row r: rows r and
-// r + 1 sit in opposite halves of the 64 banks, and the 8 row pairs of any 16
-// consecutive rows get distinct chunk slots, so both a 16-lane pass of stores
-// (two rows of 8 chunks) and of fragment reads (16 rows, one chunk) hit 64
-// distinct banks.
-__device__ inline int lds_chunk(int r, int c) { return c ^ ((r >> 1) & 7); }
-
+constexpr int BK = 64;   // K step: one LDS stage, two MFMA k-steps
 // Interleaved N index of the SwiGLU GEMM -> row of w_gate_up.
 __device__ inline int swiglu_row(int c, int mlp) {
   const int blk = c >> 4, out = ((blk >> 1) << 4) | (c & 15);
@@ -74,117 +57,6 @@ template <bool TRANS>
 __device__ __forceinline__ void mma_tile(const bf16x8& a, const bf16x8& w, f32x4& acc) {
   acc = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a, acc, 0, 0, 0)
               : __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w, acc, 0, 0, 0);
-}
-
-// acc = A[m0 .., kbeg .. kbeg + nk BK) . W[n0 .., same]^T for one BM x BN tile
-// (SWI: W rows in the interleaved gate/up order), through the LDS buffers
-// As / Ws of the calling kernel, WPF weight steps in flight in registers.
-// nk even (two steps per loop pass).
-template <int MTW, int NTW, int WM, int WN, bool SWI, int WPF>
-__device__ __forceinline__ void tile_mma(const GemmArgs& a, int n0, int m0, int kbeg, int nk,
-                                         uint16_t (&As)[2][WM * MTW * 16 * LDK],
-                                         uint16_t (&Ws)[2][WN * NTW * 16 * LDK],
-                                         f32x4 (&acc)[MTW][NTW]) {
-  constexpr int NTHR = WM * WN * 64, TM = MTW * 16, TN = NTW * 16;
-  constexpr int BM = WM * TM, BN = WN * TN;
-  constexpr int ACH = BM * (BK / 8), WCH = BN * (BK / 8);   // 16-byte chunks per stage
-  constexpr int AL = (ACH + NTHR - 1) / NTHR, WL = (WCH + NTHR - 1) / NTHR;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const uint16_t* A = static_cast<const uint16_t*>(a.A);
-  const uint16_t* W = static_cast<const uint16_t*>(a.W);
-
-  // Chunk c of a stage: row c / 8, columns (c % 8) * 8 .. + 8. Threads past
-  // the chunk count duplicate an earlier chunk (same value, same place).
-  const uint16_t* asrc[AL];
-  const uint16_t* wsrc[WL];
-  int adst[AL], wdst[WL];
-#pragma unroll
-  for (int i = 0; i < AL; ++i) {
-    const int c = (tid + i * NTHR) % ACH, row = c >> 3, col = (c & 7) * 8;
-    asrc[i] = A + (long)min(m0 + row, a.M - 1) * a.lda + kbeg + col;
-    adst[i] = row * LDK + lds_chunk(row, c & 7) * 8;
-  }
-#pragma unroll
-  for (int i = 0; i < WL; ++i) {
-    const int c = (tid + i * NTHR) % WCH, row = c >> 3, col = (c & 7) * 8;
-    const int gn = min(n0 + row, a.N - 1);
-    const int wrow = SWI ? swiglu_row(gn, a.mlp) : gn;
-    wsrc[i] = W + (long)wrow * a.ldw + kbeg + col;
-    wdst[i] = row * LDK + lds_chunk(row, c & 7) * 8;
-  }
-
-  // LDS row offsets of this lane's fragment rows (rows are multiples of 16
-  // plus lane & 15, so the swizzle depends on lane & 15 alone)
-  int ard[MTW], wrd[NTW];
-#pragma unroll
-  for (int i = 0; i < MTW; ++i) ard[i] = (wm * TM + i * 16 + (lane & 15)) * LDK;
-#pragma unroll
-  for (int j = 0; j < NTW; ++j) wrd[j] = (wn * TN + j * 16 + (lane & 15)) * LDK;
-
-  // wq[p]: weights of step kt + 1 + p; a0 / a1: activation stages kt + 1 and
-  // kt + 2 (roles swap every step). Constant indices only: registers.
-  u32x4 wq[WPF][WL];
-  u32x4 a0[AL], a1[AL];
-#pragma unroll
-  for (int i = 0; i < MTW; ++i)
-#pragma unroll
-    for (int j = 0; j < NTW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#define LDR_LOAD(dst, src, kt) dst = *reinterpret_cast<const u32x4*>((src) + (kt) * BK)
-#define LDR_STORE(buf_arr, off, v) *reinterpret_cast<u32x4*>(&buf_arr[off]) = (v)
-  // One K step: MFMAs on LDS buffer `buf` while stage kt + 2 of A and step
-  // kt + 1 + WPF of W are fetched; then stage kt + 1 (A in `cur`, W in wq[0])
-  // goes to the other buffer.
-#define LDR_STEP(kt, buf, nxt, cur)                                                   \
-  {                                                                                   \
-    _Pragma("unroll") for (int i = 0; i < AL; ++i)                                    \
-        LDR_LOAD(nxt[i], asrc[i], min((kt) + 2, nk - 1));                             \
-    _Pragma("unroll") for (int kk = 0; kk < 2; ++kk) {                                \
-      bf16x8 bfr[NTW];                                                                \
-      _Pragma("unroll") for (int j = 0; j < NTW; ++j) bfr[j] =                        \
-          __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(                 \
-              &Ws[buf][wrd[j] + lds_chunk(lane & 15, kk * 4 + (lane >> 4)) * 8]));       \
-      _Pragma("unroll") for (int i = 0; i < MTW; ++i) {                               \
-        const bf16x8 av = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>( \
-            &As[buf][ard[i] + lds_chunk(lane & 15, kk * 4 + (lane >> 4)) * 8]));         \
-        _Pragma("unroll") for (int j = 0; j < NTW; ++j)                               \
-            mma_tile<SWI>(av, bfr[j], acc[i][j]);                                     \
-      }                                                                               \
-    }                                                                                 \
-    _Pragma("unroll") for (int i = 0; i < AL; ++i) LDR_STORE(As[(buf) ^ 1], adst[i], cur[i]); \
-    _Pragma("unroll") for (int i = 0; i < WL; ++i) LDR_STORE(Ws[(buf) ^ 1], wdst[i], wq[0][i]); \
-    _Pragma("unroll") for (int p = 0; p + 1 < WPF; ++p)                               \
-        _Pragma("unroll") for (int i = 0; i < WL; ++i) wq[p][i] = wq[p + 1][i];       \
-    _Pragma("unroll") for (int i = 0; i < WL; ++i)                                    \
-        LDR_LOAD(wq[WPF - 1][i], wsrc[i], min((kt) + 1 + WPF, nk - 1));               \
-    lds_barrier();                                                                    \
-  }
-
-  // Prologue: stage 0 into LDS, A stage 1 and W steps 1..WPF in flight.
-#pragma unroll
-  for (int i = 0; i < AL; ++i) LDR_LOAD(a0[i], asrc[i], 0);
-#pragma unroll
-  for (int i = 0; i < WL; ++i) LDR_LOAD(wq[0][i], wsrc[i], 0);
-#pragma unroll
-  for (int i = 0; i < AL; ++i) LDR_STORE(As[0], adst[i], a0[i]);
-#pragma unroll
-  for (int i = 0; i < WL; ++i) LDR_STORE(Ws[0], wdst[i], wq[0][i]);
-#pragma unroll
-  for (int p = 0; p < WPF; ++p)
-#pragma unroll
-    for (int i = 0; i < WL; ++i) LDR_LOAD(wq[p][i], wsrc[i], min(1 + p, nk - 1));
-#pragma unroll
-  for (int i = 0; i < AL; ++i) LDR_LOAD(a1[i], asrc[i], min(1, nk - 1));
-  lds_barrier();
-  // Even steps fetch into a0 and park a1; odd steps the other way round.
-  // plan_gemm keeps nk even.
-  for (int kt = 0; kt < nk; kt += 2) {
-    LDR_STEP(kt, 0, a0, a1)
-    LDR_STEP(kt + 1, 1, a1, a0)
-  }
-#undef LDR_STEP
-#undef LDR_STORE
-#undef LDR_LOAD
 }
 
 // Stores one tile's accumulators: EPI_STORE / EPI_LOGITS fp32 (split z at
@@ -283,23 +155,6 @@ __device__ __forceinline__ void xcd_tile(int& x, int& y, int& z) {
   z = l / (gx * gy);
 }
 
-// WPF: weight steps in flight (8 measured no faster for the 16-row tiles,
-// which only stream weights).
-template <int MTW, int NTW, int WM, int WN, int EPI, int WPF = 4>
-__global__ void __launch_bounds__(WM * WN * 64, 1) gemm_kernel(GemmArgs a) {
-  constexpr int BM = WM * MTW * 16, BN = WN * NTW * 16;
-  static_assert(EPI != EPI_SWIGLU || NTW % 2 == 0, "swiglu pairs");
-  __shared__ __attribute__((aligned(16))) uint16_t As[2][BM * LDK];
-  __shared__ __attribute__((aligned(16))) uint16_t Ws[2][BN * LDK];
-  int bx, by, z;
-  xcd_tile(bx, by, z);
-  const int n0 = bx * BN, m0 = by * BM;
-  const int kper = a.K / a.splits, kbeg = z * kper, nk = kper / BK;
-  f32x4 acc[MTW][NTW];
-  tile_mma<MTW, NTW, WM, WN, EPI == EPI_SWIGLU, WPF>(a, n0, m0, kbeg, nk, As, Ws, acc);
-  store_tile<MTW, NTW, WM, WN, EPI>(a, n0, m0, z, acc);
-}
-
 // fp32 SIMT tile: 32 x 64 outputs per 256 threads, each 2 rows x 4 columns
 // (rows tm + 16r, columns tn + 16c), K step 16.
 template <int EPI>
@@ -383,19 +238,22 @@ __device__ inline void group_barrier() {
 // + (k & 7). The residual norms, the attention output and the SwiGLU GEMM write
 // their rows in that layout for the GEMM that reads them.
 //
-// A workgroup owns all 256 rows x BN columns of the output and a 1/splits
-// share of K, in steps of 64. Eight compute waves own 32 rows each: their A
+// A workgroup owns BM rows x BN columns of the output and a 1/splits share of
+// K, in steps of 64. NW compute waves own MTW 16-row tiles each: their A
 // fragments go straight to registers, FRA steps ahead (private, so no LDS),
-// and they read all BN weight rows of a step from LDS. The same pipeline
-// with one compute wave of 16 rows reading row-major activations (ROWA) takes
-// the GEMMs of at most 16 rows in place of the staged kernel: those only
-// stream their weights, and the DMA streams them faster (the boundary fusion
-// at batch 16 35.8 -> 33.5 us; the batch-1 SwiGLU GEMM 53.4 -> 49.8 us). NL loader waves only
+// and they read all BN weight rows of a step from LDS. NL loader waves only
 // stage the weights by DMA (global_load_lds, 8 rows of 128 bytes per
 // instruction, 16-byte chunk c of row r at c ^ (r & 7)) into a ring of NB
 // stages, NB - 1 steps ahead. A wave that issued the weight DMA itself
 // between its MFMAs ran them at about half their rate; with the DMA in waves
 // of its own the compute waves keep most of it.
+// BM follows M (16, 32, 64, 128 or 256 rows): below 256 the GEMM is the weight
+// stream alone, and the activation rows' loads share its path into the CU, so
+// a tile reads no more of them than it has rows. (64 rows, Qwen3-8B, against
+// 256-column tiles of a kernel that staged both operands through registers and
+// LDS: gate/up 64.7 -> 47.2 us, the step 1100 -> 899 us; 80 rows, against 256-row
+// tiles: the step 1021 -> 939 us.) A may also be row-major (ROWA: the boundary states in the
+// arena; every GEMM of at most 16 rows).
 // Ordering: at step kt every wave waits for its own share of what the step
 // needs (a loader: its DMA of stage kt, with the NB - 2 later stages still in
 // flight; a compute wave: its A loads of stage kt and its LDS reads of step
@@ -412,10 +270,7 @@ template <int N> __device__ inline void wait_vm_lgkm0() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
 }
 
-constexpr int kFragWaves = 8;    // compute waves of the fragment-layout GEMM
-constexpr int kFragLoaders = 4;  // its loader waves
-constexpr int kFragThreads = 64 * (kFragWaves + kFragLoaders);
-constexpr int kRowsThreads = 64 * (1 + kFragLoaders);   // the 16-row variant
+constexpr int kFragLoaders = 4;   // loader waves
 
 // NW compute waves of MTW 16-row tiles each; ROWA: activations row-major
 // (row stride lda) instead of the fragment layout.
@@ -563,15 +418,10 @@ __device__ __forceinline__ void frag_gemm(const GemmArgs& a) {
   store_tile<MTW, NTW, WM, WN, EPI>(a, n0, m0, z, acc);
 }
 
-template <int MTW, int NTW, int EPI, int FRA, int NL, int NB>
-__global__ void __launch_bounds__(64 * (kFragWaves + NL), 1) gemm_frag_kernel(GemmArgs a) {
-  frag_gemm<MTW, NTW, EPI, FRA, NL, NB, kFragWaves, false>(a);
-}
-
-// M <= 16, row-major activations: one compute wave and the loader waves.
-template <int NTW, int EPI>
-__global__ void __launch_bounds__(kRowsThreads, 1) gemm_rows16_kernel(GemmArgs a) {
-  frag_gemm<1, NTW, EPI, 2, kFragLoaders, 6, 1, true>(a);
+// NW x MTW row tiles of 16, BN = 16 NTW columns.
+template <int NW, int MTW, int NTW, int EPI, bool ROWA>
+__global__ void __launch_bounds__(64 * (NW + kFragLoaders), 1) gemm_frag_kernel(GemmArgs a) {
+  frag_gemm<MTW, NTW, EPI, 2, kFragLoaders, 6, NW, ROWA>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -960,160 +810,124 @@ __global__ void __launch_bounds__(256) tile_matrix_kernel(const uint16_t* src, l
   }
 }
 
-// Tile configurations (cfg): 0: BM 16 (M <= 16) with 4 waves along N (BN 128);
-// 1: BM 32, 2: BM 64, with 8 waves along N (BN 256); 3: BM 256 with 4 x 2 waves
-// of 64 x 64 (BN 128);
-// 4: BM 256 with 8 x 1 waves of 32 x 96 (BN 96), for the SwiGLU GEMM, whose
-// 2 x 12288 columns at the Qwen3-8B shape make exactly 256 tiles (one per CU);
-// 5: BM 256 with 4 x 2 waves of 64 x 32 (BN 64), in place of cfg 3 when cfg 3
-// would split K eight ways into pieces of at most 512: as fast there (the O
-// projection) with half the split-K partials for the next kernel to read;
-// 9: BM 16 with 3 waves along N (BN 96), in place of cfg 0 where 96-column
-// tiles fill the CUs better;
-// 10, 11: gemm_rows16_kernel, cfg 0 and 9 (BM 16, BN 128 or 96) with the
-// weights streamed by loader waves, where each split's K range is a multiple
-// of 64;
-// 6, 7, 8: gemm_frag_kernel, BM 256 with 8 compute waves of 32 x 96 (BN 96),
-// 32 x 128 (BN 128) or 32 x 64 (BN 64) and 4 loader waves, activation rows in
-// the fragment layout: the GEMMs above 64 rows whose input is written in that
-// layout (the SwiGLU GEMM in place of cfg 4 or 3; the QKV, O and down
-// projections).
-template <int EPI>
-hipError_t launch_cfg(int cfg, dim3 grid, const GemmArgs& a, hipStream_t st) {
-  switch (cfg) {
-    case 0: hipLaunchKernelGGL((gemm_kernel<1, 2, 1, 4, EPI>), grid, dim3(256), 0, st, a); break;
-    case 1: hipLaunchKernelGGL((gemm_kernel<2, 2, 1, 8, EPI>), grid, dim3(512), 0, st, a); break;
-    case 2: hipLaunchKernelGGL((gemm_kernel<4, 2, 1, 8, EPI>), grid, dim3(512), 0, st, a); break;
-    case 4: hipLaunchKernelGGL((gemm_kernel<2, 6, 8, 1, EPI>), grid, dim3(512), 0, st, a); break;
-    case 5: hipLaunchKernelGGL((gemm_kernel<4, 2, 4, 2, EPI>), grid, dim3(512), 0, st, a); break;
-    case 6:
-      hipLaunchKernelGGL((gemm_frag_kernel<2, 6, EPI, 2, kFragLoaders, 6>), grid,
-                         dim3(kFragThreads), 0, st, a);
-      break;
-    case 7:
-      hipLaunchKernelGGL((gemm_frag_kernel<2, 8, EPI, 2, kFragLoaders, 6>), grid,
-                         dim3(kFragThreads), 0, st, a);
-      break;
-    case 8:
-      hipLaunchKernelGGL((gemm_frag_kernel<2, 4, EPI, 2, kFragLoaders, 6>), grid,
-                         dim3(kFragThreads), 0, st, a);
-      break;
-    case 9: hipLaunchKernelGGL((gemm_kernel<1, 2, 1, 3, EPI>), grid, dim3(192), 0, st, a); break;
-    case 10:
-      hipLaunchKernelGGL((gemm_rows16_kernel<8, EPI>), grid, dim3(kRowsThreads), 0, st, a);
-      break;
-    case 11:
-      hipLaunchKernelGGL((gemm_rows16_kernel<6, EPI>), grid, dim3(kRowsThreads), 0, st, a);
-      break;
-    default: hipLaunchKernelGGL((gemm_kernel<4, 4, 4, 2, EPI>), grid, dim3(512), 0, st, a); break;
-  }
+// Launches gemm_frag_kernel for the plan's BM x BN tile. EPI_SWIGLU rows are in
+// the fragment layout or, for at most 16 rows, row-major.
+template <int EPI, bool ROWA, int NW, int MTW>
+hipError_t launch_bn(const GemmPlan& p, dim3 grid, const GemmArgs& a, hipStream_t st) {
+  const dim3 block(64 * (NW + kFragLoaders));
+  if (p.bn == 128)
+    hipLaunchKernelGGL((gemm_frag_kernel<NW, MTW, 8, EPI, ROWA>), grid, block, 0, st, a);
+  else if (p.bn == 96)
+    hipLaunchKernelGGL((gemm_frag_kernel<NW, MTW, 6, EPI, ROWA>), grid, block, 0, st, a);
+  else if constexpr (NW * MTW > 4)   // 64 columns: above 64 rows only
+    hipLaunchKernelGGL((gemm_frag_kernel<NW, MTW, 4, EPI, ROWA>), grid, block, 0, st, a);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+template <int EPI>
+hipError_t launch_frag(const GemmPlan& p, dim3 grid, const GemmArgs& a, hipStream_t st) {
+  if (p.bm == 16) return launch_bn<EPI, true, 1, 1>(p, grid, a, st);
+  if constexpr (EPI == EPI_STORE) {
+    if (!p.frag) {
+      switch (p.bm) {
+        case 32: return launch_bn<EPI, true, 2, 1>(p, grid, a, st);
+        case 64: return launch_bn<EPI, true, 4, 1>(p, grid, a, st);
+        case 128: return launch_bn<EPI, true, 8, 1>(p, grid, a, st);
+        default: return launch_bn<EPI, true, 8, 2>(p, grid, a, st);
+      }
+    }
+  }
+  switch (p.bm) {
+    case 32: return launch_bn<EPI, false, 2, 1>(p, grid, a, st);
+    case 64: return launch_bn<EPI, false, 4, 1>(p, grid, a, st);
+    case 128: return launch_bn<EPI, false, 8, 1>(p, grid, a, st);
+    default: return launch_bn<EPI, false, 8, 2>(p, grid, a, st);
+  }
 }
 
 }  // namespace
 
-// bf16: the smallest BM of {16, 32, 64, 256} that covers M (several M tiles
-// past 256); the SwiGLU GEMM at BM 256 uses the 96-column tile. Split-K (1, 2, 4 or 8) only where allowed, to about one workgroup
-// per CU, keeping an even number of at least 4 K steps per split.
+// bf16: BM is the smallest of 16, 32, 64, 128 and 256 that covers M (several
+// row tiles past 256); BN and the K split (1, 2, 4, 8; only where allowed) are
+// chosen among 128, 96 and 64 columns.
 GemmPlan plan_gemm(int dtype, int M, int N, int K, bool allow_split, bool swiglu, bool frag,
                    int max_splits) {
-  GemmPlan p;
+  GemmPlan p{};
   constexpr int kCUs = 256;
-  if (frag && !swiglu && dtype == LDR_BF16 && M > 64 && K % BK == 0) {
-    // Activation rows in the fragment layout: 256 x BN tiles of 128, 96 or 64
-    // columns and a K split of 1 .. 8 that keeps the workgroups within one
+  p.splits = 1;
+  if (!allow_split) max_splits = 1;
+  if (dtype == LDR_F32) {
+    p.bm = 32; p.bn = 64;
+    p.grid_x = (N + p.bn - 1) / p.bn; p.grid_y = (M + p.bm - 1) / p.bm;
+    const long tiles = (long)p.grid_x * p.grid_y;
+    while (p.splits < max_splits && tiles * p.splits * 2 <= kCUs && K % (2 * p.splits * 16) == 0 &&
+           K / (2 * p.splits) >= 32)
+      p.splits *= 2;
+    return p;
+  }
+  p.bm = M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : M <= 128 ? 128 : 256;
+  p.frag = p.bm > 16 && (swiglu || frag);
+  p.grid_y = (M + p.bm - 1) / p.bm;
+  const int widths[3] = {128, 96, 64};
+  if (p.bm <= 64) {
+    // Few rows: the weight stream. 128 columns, or 96 where they fill more of
+    // the workgroups' last round over the CUs (the batch-1 QKV projection 48 x 4
+    // workgroups against 64 x 4: 14.6 -> 13.2 us; the SwiGLU GEMM 47.6 and 47.7
+    // us either way), and the K split that brings them to about one per CU, an
+    // even number of at least 4 K steps each.
+    double best = -1.0;
+    for (int w = 0; w < 2; ++w) {
+      const long tiles = (long)((N + widths[w] - 1) / widths[w]) * p.grid_y;
+      int sp = 1;
+      while (sp < max_splits && tiles * sp * 2 <= kCUs && K % (2 * sp * 2 * BK) == 0 &&
+             K / (2 * sp) >= 4 * BK)
+        sp *= 2;
+      const long wg = tiles * sp;
+      const double fill = (double)wg / (double)(((wg + kCUs - 1) / kCUs) * kCUs);
+      if (fill > best + 1e-9) { best = fill; p.bn = widths[w]; p.splits = sp; }
+    }
+  } else if (swiglu) {
+    // no split-K: the column width whose rounds over the CUs times the bytes a
+    // tile streams (all its activation rows plus its weight columns) is least
+    double best = 0.0;
+    const int order[3] = {96, 128, 64};
+    for (const int w : order) {
+      const long tiles = (long)p.grid_y * ((N + w - 1) / w);
+      const double cost = (double)((tiles + kCUs - 1) / kCUs) * (p.bm + w) * K;
+      if (best == 0.0 || cost < best) { best = cost; p.bn = w; }
+    }
+  } else {
+    // 128, 96 or 64 columns and a K split that keeps the workgroups within one
     // round over the CUs (no split where the tiles alone take more). Taken in
     // order: the plan whose workgroups fill the most of their last round; then
     // one whose K range is at most 2048 (longer ranges measured slower, each
     // workgroup re-reading more activation rows); then the fewest splits (the
     // fp32 partial tiles are written in a burst at the end and read back by
     // the next kernel); then the fewest bytes per workgroup.
-    const int cands[3][2] = {{7, 128}, {6, 96}, {8, 64}};
     double best_u = -1.0, best_v = 0.0;
     bool best_short = false;
-    for (const auto& c : cands) {
-      const long tiles = (long)((N + c[1] - 1) / c[1]) * ((M + 255) / 256);
-      for (int sp = 1; sp <= (allow_split ? max_splits : 1); sp *= 2) {
+    for (const int w : widths) {
+      const long tiles = (long)((N + w - 1) / w) * p.grid_y;
+      for (int sp = 1; sp <= max_splits; sp *= 2) {
         if (K % (sp * BK) != 0 || K / sp < 2 * BK) break;
         const long wg = tiles * sp;
         if (sp > 1 && wg > kCUs) break;
         const double u = (double)wg / (double)(((wg + kCUs - 1) / kCUs) * kCUs);
         const bool shrt = K / sp <= 2048;
-        const double vol = (256.0 + c[1]) * (K / sp) * 2.0;
+        const double vol = ((double)p.bm + w) * (K / sp) * 2.0;
         bool take;
         if (u > best_u + 1e-9) take = true;
         else if (u < best_u - 1e-9) take = false;
         else if (shrt != best_short) take = shrt;
         else if (sp != p.splits) take = sp < p.splits;
         else take = vol < best_v;
-        if (take) {
-          best_u = u; best_v = vol; best_short = shrt; p.cfg = c[0]; p.splits = sp;
-          p.grid_x = (N + c[1] - 1) / c[1]; p.grid_y = (M + 255) / 256;
-        }
+        if (take) { best_u = u; best_v = vol; best_short = shrt; p.bn = w; p.splits = sp; }
       }
     }
-    if (best_u > 0.0) { p.ntw = 0; return p; }
   }
-  int bm, bn, kstep;
-  if (dtype == LDR_F32) {
-    p.cfg = -1; bm = 32; bn = 64; kstep = 16;
-  } else {
-    p.cfg = M <= 16 ? 0 : M <= 32 ? 1 : M <= 64 ? 2 : swiglu ? 4 : 3;
-    if (p.cfg == 4) {
-      // SwiGLU tiles (no split-K): the column width whose rounds over the CUs
-      // times the bytes a tile streams (all its activation rows plus its
-      // weight columns) is least, among 96 (cfg 4), 128 (cfg 3) and 64 (cfg 5)
-      const int mt = (M + 255) / 256;
-      double best = 0.0;
-      const int cands[3][2] = {{4, 96}, {3, 128}, {5, 64}};
-      for (const auto& c : cands) {
-        const long tiles = (long)mt * ((N + c[1] - 1) / c[1]);
-        const double cost = (double)((tiles + kCUs - 1) / kCUs) * (256.0 + c[1]) * K;
-        if (best == 0.0 || cost < best) { best = cost; p.cfg = c[0]; }
-      }
-    }
-    // the SwiGLU GEMM above 64 rows reads its rows in the fragment layout
-    if (swiglu && M > 64 && K % BK == 0) p.cfg = p.cfg == 4 ? 6 : p.cfg == 3 ? 7 : p.cfg;
-    if (p.cfg == 3 && allow_split && !swiglu) {
-      const int t128 = ((N + 127) / 128) * ((M + 255) / 256);
-      if (t128 * 8 <= kCUs && t128 * 16 > kCUs && K / 8 <= 512 && K % (4 * 2 * 2 * BK) == 0)
-        p.cfg = 5;
-    }
-    bm = p.cfg >= 3 ? 256 : 16 << p.cfg;
-    bn = p.cfg == 5 ? 64 : (p.cfg == 4 || p.cfg == 6) ? 96
-         : (p.cfg == 3 || p.cfg == 0 || p.cfg == 7) ? 128 : 256;
-    kstep = 2 * BK;
-  }
-  // split-K factor for `tiles` tiles: up to about one workgroup per CU, an
-  // even number of at least 2 K steps per split
-  auto split_for = [&](long tiles) {
-    int s = 1;
-    if (allow_split)
-      while (s < max_splits && tiles * s * 2 <= kCUs && K % (2 * s * kstep) == 0 &&
-             K / (2 * s) >= 2 * kstep)
-        s *= 2;
-    return s;
-  };
-  if (p.cfg == 0) {
-    // 16-row tiles of 128 columns (4 waves) or 96 columns (cfg 9, 3 waves):
-    // the width whose workgroups fill more of their last round over the CUs
-    // (128 on a tie). At batch 1 the SwiGLU GEMM's 24576 columns make 192
-    // tiles of 128 but 256 of 96 (47.6 and 47.7 us: these tiles stream their
-    // weights at the chip's rate either way), and the QKV projection 48 x 4
-    // against 64 x 4 (14.6 -> 13.2 us).
-    auto fill = [&](int w) {
-      const long tiles = (long)((N + w - 1) / w) * ((M + 15) / 16);
-      const long wg = tiles * split_for(tiles);
-      return (double)wg / (double)(((wg + kCUs - 1) / kCUs) * kCUs);
-    };
-    if (fill(96) > fill(128) + 1e-9) { p.cfg = 9; bn = 96; }
-  }
-  p.ntw = 0;
-  p.grid_x = (N + bn - 1) / bn;
-  p.grid_y = (M + bm - 1) / bm;
-  p.splits = split_for((long)p.grid_x * p.grid_y);
-  // 16-row tiles stream their weights through the loader waves' DMA
-  if ((p.cfg == 0 || p.cfg == 9) && (K / p.splits) % BK == 0) p.cfg = p.cfg == 0 ? 10 : 11;
+  p.grid_x = (N + p.bn - 1) / p.bn;
   return p;
 }
 
@@ -1128,9 +942,8 @@ hipError_t launch_gemm(int dtype, int epi, const GemmPlan& p, const GemmArgs& a,
     return hipGetLastError();
   }
   const dim3 grid(p.grid_x, p.grid_y, p.splits);
-  if (epi == EPI_SWIGLU) return launch_cfg<EPI_SWIGLU>(p.cfg, grid, a, st);
-  if (epi == EPI_LOGITS) return launch_cfg<EPI_LOGITS>(p.cfg, grid, a, st);
-  return launch_cfg<EPI_STORE>(p.cfg, grid, a, st);
+  if (epi == EPI_SWIGLU) return launch_frag<EPI_SWIGLU>(p, grid, a, st);
+  return launch_frag<EPI_STORE>(p, grid, a, st);   // EPI_LOGITS: the same store, never split
 }
 
 bool gemm_tiled_supported(int M, int N, int K) {

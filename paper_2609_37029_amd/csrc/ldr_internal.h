@@ -186,10 +186,10 @@ struct GemmArgs {
   int mlp;                     // EPI_SWIGLU: N / 2
   int out_frag = 0;            // EPI_SWIGLU: output [M][mlp] in the fragment layout
 };
-struct GemmPlan { int cfg, ntw, splits; int grid_x, grid_y; };  // cfg: tile configuration
-// The plan's kernel reads its activation rows in the fragment layout (NRM_FRAG).
-inline bool gemm_plan_frag(const GemmPlan& p) { return p.cfg >= 6 && p.cfg <= 8; }
-// Tile configuration and split-K factor; splits = 1 unless allow_split, at
+// Output tile bm x bn, K splits, grid, and whether the kernel reads its
+// activation rows in the fragment layout (NRM_FRAG; else row-major).
+struct GemmPlan { int bm, bn, splits; int grid_x, grid_y; bool frag; };
+// Tile and split-K factor; splits = 1 unless allow_split, at
 // most max_splits (a power of two). frag: the caller can give the activation
 // rows in the fragment layout.
 GemmPlan plan_gemm(int dtype, int M, int N, int K, bool allow_split, bool swiglu = false,

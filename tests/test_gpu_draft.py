@@ -60,6 +60,22 @@ def test_logits_match_oracle(gpu_lib, shape, batch, prefix):
         check_logits(zc[b], ref[b], shape)
 
 
+# (batch, block): rows at both sides of the row tiles of 32, 64 and 128, and
+# boundary fusions (one row per sequence) of more than 16, 64 and 128 rows
+@pytest.mark.parametrize("batch,block", [(2, 16), (3, 11), (4, 16), (5, 13), (8, 16), (9, 15),
+                                         (20, 2), (70, 1), (130, 1)])
+def test_row_tiles_match_oracle(gpu_lib, batch, block):
+    s = MINI_BF16.replace(block=block, n_layers=1)
+    p, w, dw, anchor = setup(gpu_lib, s, batch, 60, decode=1)
+    z = gpu_lib.draft_step(p.views, dw, anchor)
+    torch.cuda.synchronize()
+    seqs = sorted({0, batch // 2, batch - 1})
+    ref = oracle_logits(p, w, anchor, seqs=seqs)
+    zc = z.cpu().numpy()
+    for b in seqs:
+        check_logits(zc[b], ref[b], s)
+
+
 # 90000 tokens: 297 column tiles of 304, more than one round over the 256 CUs,
 # the last tile 16 columns wide, its staged weight rows past the padded matrix
 MINI_BF16_WIDE_V = MINI_BF16.replace(name="mini-bf16-v90000", vocab=90000)
