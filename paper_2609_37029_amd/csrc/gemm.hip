@@ -155,57 +155,92 @@ __device__ __forceinline__ void xcd_tile(int& x, int& y, int& z) {
   z = l / (gx * gy);
 }
 
-// fp32 SIMT tile: 32 x 64 outputs per 256 threads, each 2 rows x 4 columns
-// (rows tm + 16r, columns tn + 16c), K step 16.
-template <int EPI>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs a) {
-  constexpr int FBM = 32, FBN = 64, FBK = 16;
-  __shared__ float As[FBK][FBM + 1];
-  __shared__ float Ws[FBK][FBN + 1];
-  const int tid = threadIdx.x, tm = tid >> 4, tn = tid & 15;
-  const int n0 = blockIdx.x * FBN, m0 = blockIdx.y * FBM, z = blockIdx.z;
-  const int kper = a.K / a.splits, kbeg = z * kper;
-  const float* A = static_cast<const float*>(a.A);
-  const float* W = static_cast<const float*>(a.W);
-  float acc[2][4] = {};
-  for (int k0 = kbeg; k0 < kbeg + kper; k0 += FBK) {
-    for (int i = tid; i < FBM * FBK; i += 256) {
-      const int r = i / FBK, k = i % FBK, gm = m0 + r;
-      As[k][r] = (gm < a.M) ? A[(long)gm * a.lda + k0 + k] : 0.f;
-    }
-    for (int i = tid; i < FBN * FBK; i += 256) {
-      const int r = i / FBK, k = i % FBK, gn = n0 + r;
-      int wrow = -1;
-      if (gn < a.N) wrow = EPI == EPI_SWIGLU ? swiglu_row(gn, a.mlp) : gn;
-      Ws[k][r] = wrow >= 0 ? W[(long)wrow * a.ldw + k0 + k] : 0.f;
-    }
-    __syncthreads();
+// fp32 on v_mfma_f32_16x16x4_f32 (full fp32 products and sums). A workgroup
+// owns MT x NT tiles of 16 x 16 outputs; its 8 waves take the 16-deep K chunks
+// in turn and add their tiles up in LDS, in wave order. A lane loads 16 bytes of
+// a row's chunk (4 lanes a row), its four elements serving four MFMAs: the order
+// of the contraction index is free as long as both operands share it. No LDS
+// staging: these models are small, a launch is one load latency, U chunks of
+// loads in flight a wave, and the reduction. What bounds it is that latency: a
+// SIMT kernel that staged 16-deep steps through LDS, one round trip each, took
+// 24.4 us for the Tiny model's SwiGLU GEMM (8 x 2048 x 256) and 5.2 now.
+constexpr int kF32Waves = 8;
+template <int MT, int NT, int EPI>
+__global__ void __launch_bounds__(kF32Waves * 64) gemm_f32_kernel(GemmArgs a) {
+  static_assert(EPI != EPI_SWIGLU || NT % 2 == 0, "swiglu pairs");
+  constexpr int U = 4;
+  __shared__ float red[kF32Waves][MT * NT * 256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n0 = blockIdx.x * NT * 16, m0 = blockIdx.y * MT * 16, z = blockIdx.z;
+  const int kper = a.K / a.splits, kbeg = z * kper, chunks = kper / 16;
+  const int lr = lane & 15, kq = (lane >> 4) * 4;
+  const float* ap[MT];
+  const float* wp[NT];
 #pragma unroll
-    for (int k = 0; k < FBK; ++k)
+  for (int i = 0; i < MT; ++i)   // rows past M repeat the last one (not stored)
+    ap[i] = static_cast<const float*>(a.A) + (long)min(m0 + i * 16 + lr, a.M - 1) * a.lda + kbeg + kq;
 #pragma unroll
-      for (int r = 0; r < 2; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] += As[k][tm + 16 * r] * Ws[k][tn + 16 * c];
-    __syncthreads();
+  for (int j = 0; j < NT; ++j) {
+    const int gn = min(n0 + j * 16 + lr, a.N - 1);
+    const int row = EPI == EPI_SWIGLU ? swiglu_row(gn, a.mlp) : gn;
+    wp[j] = static_cast<const float*>(a.W) + (long)row * a.ldw + kbeg + kq;
   }
+  f32x4 acc[MT][NT];
 #pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int row = m0 + tm + 16 * r;
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c0 = wave; c0 < chunks; c0 += U * kF32Waves) {
+    f32x4 av[U][MT], wv[U][NT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {   // chunks past the end repeat the last one (not used)
+      const int k = min(c0 + u * kF32Waves, chunks - 1) * 16;
+#pragma unroll
+      for (int i = 0; i < MT; ++i) av[u][i] = *reinterpret_cast<const f32x4*>(ap[i] + k);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) wv[u][j] = *reinterpret_cast<const f32x4*>(wp[j] + k);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c0 + u * kF32Waves < chunks)   // wave-uniform
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], wv[u][j][e], acc[i][j],
+                                                               0, 0, 0);
+  }
+  // tile (i, j): element (row (lane / 16) * 4 + v, column lane % 16) at v * 64 + lane
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[wave][(i * NT + j) * 256 + v * 64 + lane] = acc[i][j][v];
+  __syncthreads();
+  auto total = [&](int e) {
+    float s = red[0][e];
+#pragma unroll
+    for (int w = 1; w < kF32Waves; ++w) s += red[w][e];
+    return s;
+  };
+  constexpr int NP = EPI == EPI_SWIGLU ? NT / 2 : NT;   // output column tiles
+  for (int o = tid; o < MT * NP * 256; o += kF32Waves * 64) {
+    const int t = o >> 8, i = t / NP, j = t % NP, l = o & 63, v = (o >> 6) & 3;
+    const int row = m0 + i * 16 + (l >> 4) * 4 + v;
     if (row >= a.M) continue;
-    if constexpr (EPI == EPI_STORE) {
-      float* out = static_cast<float*>(a.out) + (long)z * a.split_stride;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int col = n0 + tn + 16 * c;
-        if (col < a.N) out[(long)row * a.ldo + col] = acc[r][c];
-      }
+    if constexpr (EPI == EPI_SWIGLU) {   // column tiles 2 j (gate) and 2 j + 1 (up)
+      const int col = (n0 >> 1) + j * 16 + (l & 15);
+      const int e = (i * NT + 2 * j) * 256 + v * 64 + l;
+      if (col < a.mlp)
+        static_cast<float*>(a.out)[(long)row * a.ldo + col] = silu(total(e)) * total(e + 256);
     } else {
-      float* out = static_cast<float*>(a.out);
-#pragma unroll
-      for (int c = 0; c < 4; c += 2) {  // columns tn + 16c (gate) and tn + 16(c+1) (up)
-        const int col = (n0 + 16 * c) / 2 + tn;
-        if (col < a.mlp) out[(long)row * a.ldo + col] = silu(acc[r][c]) * acc[r][c + 1];
-      }
+      const int col = n0 + j * 16 + (l & 15);
+      if (col < a.N)
+        static_cast<float*>(a.out)[(long)z * a.split_stride + (long)row * a.ldo + col] =
+            total((i * NT + j) * 256 + v * 64 + l);
     }
   }
 }
@@ -859,11 +894,16 @@ GemmPlan plan_gemm(int dtype, int M, int N, int K, bool allow_split, bool swiglu
   p.splits = 1;
   if (!allow_split) max_splits = 1;
   if (dtype == LDR_F32) {
-    p.bm = 32; p.bn = 64;
-    p.grid_x = (N + p.bn - 1) / p.bn; p.grid_y = (M + p.bm - 1) / p.bm;
+    // 16 or 32 rows; 16 columns, or 32 for SwiGLU pairs and where 16-column tiles
+    // would put more than four workgroups on a CU; K is split only while the
+    // tiles leave half of the CUs idle and a split keeps 512 (4 chunks a wave)
+    p.bm = M <= 16 ? 16 : 32;
+    p.grid_y = (M + p.bm - 1) / p.bm;
+    p.bn = swiglu || (long)((N + 15) / 16) * p.grid_y > 4 * kCUs ? 32 : 16;
+    p.grid_x = (N + p.bn - 1) / p.bn;
     const long tiles = (long)p.grid_x * p.grid_y;
     while (p.splits < max_splits && tiles * p.splits * 2 <= kCUs && K % (2 * p.splits * 16) == 0 &&
-           K / (2 * p.splits) >= 32)
+           K / (2 * p.splits) >= 512)
       p.splits *= 2;
     return p;
   }
@@ -934,11 +974,17 @@ GemmPlan plan_gemm(int dtype, int M, int N, int K, bool allow_split, bool swiglu
 hipError_t launch_gemm(int dtype, int epi, const GemmPlan& p, const GemmArgs& a,
                        hipStream_t st) {
   if (dtype == LDR_F32) {
-    const dim3 grid(p.grid_x, p.grid_y, p.splits);
-    if (epi == EPI_SWIGLU)
-      hipLaunchKernelGGL((gemm_f32_kernel<EPI_SWIGLU>), grid, dim3(256), 0, st, a);
-    else  // EPI_STORE and EPI_LOGITS share the fp32 store
-      hipLaunchKernelGGL((gemm_f32_kernel<EPI_STORE>), grid, dim3(256), 0, st, a);
+    const dim3 grid(p.grid_x, p.grid_y, p.splits), block(kF32Waves * 64);
+#define LDR_F32K(MT, NT, EPI) \
+  hipLaunchKernelGGL((gemm_f32_kernel<MT, NT, EPI>), grid, block, 0, st, a)
+    if (epi == EPI_SWIGLU) {
+      if (p.bm == 16) LDR_F32K(1, 2, EPI_SWIGLU); else LDR_F32K(2, 2, EPI_SWIGLU);
+    } else if (p.bn == 16) {   // EPI_STORE and EPI_LOGITS share the fp32 store
+      if (p.bm == 16) LDR_F32K(1, 1, EPI_STORE); else LDR_F32K(2, 1, EPI_STORE);
+    } else {
+      if (p.bm == 16) LDR_F32K(1, 2, EPI_STORE); else LDR_F32K(2, 2, EPI_STORE);
+    }
+#undef LDR_F32K
     return hipGetLastError();
   }
   const dim3 grid(p.grid_x, p.grid_y, p.splits);

@@ -678,8 +678,10 @@ __global__ void __launch_bounds__(kMkThreads) markov_correct_kernel(
   }
 }
 
-// Greedy partial: the first argmax of chunk [sp * chunk, ..) of the row.
-__global__ void __launch_bounds__(kThreads) sample_partial_kernel(SampleArgs a) {
+// Greedy partial: the first argmax of chunk [sp * chunk, ..) of the row; a row
+// of one chunk is then done (its token, its logit as lse, log q = 0).
+__global__ void __launch_bounds__(kThreads) sample_partial_kernel(SampleArgs a, int32_t* tokens,
+                                                                  float* lse, float* logq) {
   const int sp = blockIdx.x, r = blockIdx.y;
   const int v0 = sp * a.chunk, v1 = min(a.vocab, v0 + a.chunk);
   const float* z = a.logits + ((long)r * a.row_mul + a.row_add) * a.vocab;
@@ -695,7 +697,14 @@ __global__ void __launch_bounds__(kThreads) sample_partial_kernel(SampleArgs a) 
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < kThreads / 64; ++w) combine(p, red[w]);
-    a.part[(long)r * a.splits + sp] = p;
+    if (a.splits > 1) {
+      a.part[(long)r * a.splits + sp] = p;
+    } else {
+      const long g = (long)r * a.row_mul + a.row_add;
+      tokens[g] = p.idx;
+      lse[g] = p.key;
+      logq[g] = 0.f;
+    }
   }
 }
 
@@ -748,7 +757,9 @@ SamplePlan sample_plan(int rows, int vocab) {
   const long target = ((long)vocab * rows + 2047) / 2048;
   int chunk = sweep;
   while (chunk * 2L <= target && chunk < 32 * sweep) chunk *= 2;
-  if (rows >= 2048) chunk = (vocab + sweep - 1) / sweep * sweep;
+  // (and for a vocabulary of at most four sweeps, where the merge's launch
+  // costs more than walking them)
+  if (rows >= 2048 || vocab <= 4 * sweep) chunk = (vocab + sweep - 1) / sweep * sweep;
   p.greedy_chunk = chunk;
   p.greedy_splits = (vocab + chunk - 1) / chunk;
   // T > 0: 16-token chunks, their log-masses in rows padded to 4 floats
@@ -864,9 +875,10 @@ hipError_t sample_finish(const SampleArgs& a, int32_t* tokens, float* lse, float
                        lse, logq);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(sample_partial_kernel, dim3(a.splits, a.rows), dim3(kThreads), 0, st, a);
+  hipLaunchKernelGGL(sample_partial_kernel, dim3(a.splits, a.rows), dim3(kThreads), 0, st, a,
+                     tokens, lse, logq);
   const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || a.splits == 1) return e;
   hipLaunchKernelGGL(sample_merge_kernel, dim3(a.rows), dim3(64), 0, st, a, tokens, lse, logq);
   return hipGetLastError();
 }

@@ -76,6 +76,24 @@ def test_row_tiles_match_oracle(gpu_lib, batch, block):
         check_logits(zc[b], ref[b], s)
 
 
+# fp32: one and two row tiles of 16 with remainders, ragged and paired column
+# tiles, a window whose rows do not start on 16 bytes, grouped heads of 128,
+# K split over workgroups (mlp 2048)
+@pytest.mark.parametrize("batch,block,kw", [
+    (1, 1, dict(vocab=17, window=63)), (5, 7, dict(vocab=4099, window=66)),
+    (70, 1, dict(vocab=20011)), (2, 16, dict(n_q_heads=8, n_kv_heads=2, head_dim=128, mlp=2048)),
+])
+def test_fp32_tiles_match_oracle(gpu_lib, batch, block, kw):
+    s = synth.TINY.replace(block=block, **kw)
+    p, w, dw, anchor = setup(gpu_lib, s, batch, 90, decode=2)
+    z = gpu_lib.draft_step(p.views, dw, anchor)
+    torch.cuda.synchronize()
+    ref = oracle_logits(p, w, anchor, seqs=[0, batch - 1])
+    zc = z.cpu().numpy()
+    for b in (0, batch - 1):
+        check_logits(zc[b], ref[b], s)
+
+
 # 90000 tokens: 297 column tiles of 304, more than one round over the 256 CUs,
 # the last tile 16 columns wide, its staged weight rows past the padded matrix
 MINI_BF16_WIDE_V = MINI_BF16.replace(name="mini-bf16-v90000", vocab=90000)
