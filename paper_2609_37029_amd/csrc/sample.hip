@@ -51,6 +51,42 @@ __device__ inline void combine(Partial& a, const Partial& b) {
   a.m = m;
 }
 
+// Reductions over the 64 lanes of a wave: DPP inside each row of 16, then two
+// lane exchanges. Every lane ends with the same value.
+__device__ inline float wave_max64(float v) {
+  v = max16(v);
+  v = fmaxf(v, __shfl_xor(v, 16));
+  return fmaxf(v, __shfl_xor(v, 32));
+}
+__device__ inline float wave_sum64(float v) {
+  v = sum16(v);
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
+}
+__device__ inline int min16(int v) {
+  v = min(v, __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, false));
+  v = min(v, __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, false));
+  v = min(v, __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, false));
+  return min(v, __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, false));
+}
+
+// The lanes' partials combined over rows of 16 lanes (W = 16) or the whole wave
+// (W = 64), every lane with the result: the max first, then each sum rescaled
+// once, the best key and the lowest index among its equals.
+template <int W> __device__ inline Partial lanes_combine(const Partial& p) {
+  Partial o;
+  o.m = W == 64 ? wave_max64(p.m) : max16(p.m);
+  const float s = o.m == -INFINITY ? 0.f : p.s * __expf(p.m - o.m);
+  o.s = W == 64 ? wave_sum64(s) : sum16(s);
+  o.key = W == 64 ? wave_max64(p.key) : max16(p.key);
+  o.idx = min16(p.key == o.key ? p.idx : 0x7fffffff);
+  if (W == 64) {
+    o.idx = min(o.idx, __shfl_xor(o.idx, 16));
+    o.idx = min(o.idx, __shfl_xor(o.idx, 32));
+  }
+  return o;
+}
+
 struct SampleArgs {
   const float* logits; int rows, vocab, chunk, splits;
   float T; uint64_t seed, step;
@@ -378,30 +414,16 @@ __device__ void argmax_tokens(const SampleArgs& a, const float* z, int v0, int v
 // which proves that its exact key loses (the margin, 1e-3 plus 1e-6
 // relative, covers the rounding of the test and of the fixed-sequence log,
 // whose error is below 1e-5 here). Chunks without support tokens
-// (L_c = -inf) take no part. Candidates go through a per-wave queue in LDS so
-// that their exact keys (two logs each) are computed 64 at a time by full
-// waves. G entries per lane and sweep (a multiple of 4, the noise words of
-// G / 4 Philox blocks): with 12, one sweep of 1024 lanes covers 12288 chunks,
-// a 196K-token vocabulary.
+// (L_c = -inf) take no part. The bound is within 0.06 of the exact key and the
+// lanes' best entries are settled by then, so few waves meet a candidate: its
+// key is computed on the spot (collecting candidates in an LDS queue for full
+// waves cost twelve ballots and their branches a sweep, more than it saved).
+// G entries per lane and sweep (a multiple of 4, the noise words of G / 4 Philox
+// blocks): with 12, one sweep of 1024 lanes covers 12288 chunks, a 196K-token
+// vocabulary.
 template <int NT, int G = kGroup>
 __device__ void chunk_keys(const SampleArgs& a, const float* Lr, int r, int c0, int c1,
                            Partial& p) {
-  struct Cand { float zt; uint32_t bits; int v; };
-  __shared__ Cand queue[NT / 64][128];
-  const int lane = threadIdx.x & 63;
-  Cand* q = queue[threadIdx.x >> 6];
-  int qn = 0;  // wave-uniform queue length
-  auto drain = [&](int count) {  // evaluate entries [0, count), count <= 64
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (lane < count) {
-      const Cand c = q[lane];
-      const float key = __fadd_rn(c.zt, gumbel_from_bits(c.bits));
-      if (better(key, c.v, p.key, p.idx)) { p.key = key; p.idx = c.v; }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  };
   constexpr int kSweep = NT * G;
   const int lane_off = (int)threadIdx.x * G;
   const uint64_t nrow = (uint64_t)r * a.row_mul + a.row_add;
@@ -418,51 +440,34 @@ __device__ void chunk_keys(const SampleArgs& a, const float* Lr, int r, int c0, 
     float gm = -INFINITY, ub[G];
     bool in[G];
     int top = -1;
-    float top_ub = -INFINITY;
+    float top_ub = -INFINITY, zsel = 0.f;
+    uint32_t bsel = 0u;
 #pragma unroll
     for (int i = 0; i < G; ++i) {
       in[i] = v + i < c1 && zt[i] > -INFINITY;
       gm = fmaxf(gm, in[i] ? zt[i] : -INFINITY);
       ub[i] = zt[i] + gumbel_upper(bits[i]);
-      if (in[i] && (top < 0 || ub[i] > top_ub)) { top = i; top_ub = ub[i]; }
+      if (in[i] && (top < 0 || ub[i] > top_ub)) {
+        top = i; top_ub = ub[i]; zsel = zt[i]; bsel = bits[i];
+      }
     }
     if (gm > p.m) { p.s *= __expf(p.m - gm); p.m = gm; }
     // the lane's most promising entry, exactly; then the wave's best key
-    float zsel = 0.f;
-    uint32_t bsel = 0u;
-#pragma unroll
-    for (int i = 0; i < G; ++i)
-      if (i == top) { zsel = zt[i]; bsel = bits[i]; }
     if (top >= 0) {
       const float key = __fadd_rn(zsel, gumbel_from_bits(bsel));
       if (better(key, v + top, p.key, p.idx)) { p.key = key; p.idx = v + top; }
     }
-    float bound = p.key;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) bound = fmaxf(bound, __shfl_xor(bound, off));
+    const float bound = wave_max64(p.key);
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-      const bool valid = in[i];
-      if (valid) p.s += __expf(zt[i] - p.m);
+      if (in[i]) p.s += __expf(zt[i] - p.m);
       const float margin = 1e-3f + 1e-6f * (fabsf(zt[i]) + fabsf(bound));
-      const bool need = valid && i != top && !(ub[i] + margin < bound);
-      const uint64_t mask = __ballot(need);
-      if (need) {
-        const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        q[pos] = Cand{zt[i], bits[i], v + i};
-      }
-      qn += __popcll(mask);
-      if (qn >= 64) {
-        drain(64);
-        if (lane < qn - 64) q[lane] = q[64 + lane];
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        qn -= 64;
+      if (in[i] && i != top && !(ub[i] + margin < bound)) {
+        const float key = __fadd_rn(zt[i], gumbel_from_bits(bits[i]));
+        if (better(key, v + i, p.key, p.idx)) { p.key = key; p.idx = v + i; }
       }
     }
   }
-  if (qn > 0) drain(qn);
 }
 
 // Chunk log-masses of tokens [v0, v1) of one row (v0 a multiple of 16): each
@@ -523,17 +528,13 @@ __global__ void __launch_bounds__(kDrawThreads) chunk_draw_kernel(SampleArgs a, 
   const int r = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   Partial p{-INFINITY, 0.f, -INFINITY, 0x7fffffff};
   chunk_keys<kDrawThreads, 12>(a, a.L + (long)r * a.ldL, r, 0, a.nch, p);
-  for (int off = 32; off >= 1; off >>= 1) {
-    Partial o{__shfl_xor(p.m, off), __shfl_xor(p.s, off), __shfl_xor(p.key, off),
-              __shfl_xor(p.idx, off)};
-    combine(p, o);
-  }
+  p = lanes_combine<64>(p);
   __shared__ Partial red[kDrawThreads / 64];
+  static_assert(kDrawThreads / 64 == 16, "one row of lanes holds the waves' partials");
   if (lane == 0) red[wave] = p;
   __syncthreads();
   if (wave != 0) return;
-  p = red[0];
-  for (int w = 1; w < kDrawThreads / 64; ++w) combine(p, red[w]);
+  p = lanes_combine<16>(red[lane & 15]);
   const long g = (long)r * a.row_mul + a.row_add;
   const float* z = a.logits + g * a.vocab;
   // the chunk's tokens: lane i < 16 takes token 16 c + i (no chunk: none)
@@ -566,113 +567,157 @@ __global__ void __launch_bounds__(kDrawThreads) chunk_draw_kernel(SampleArgs a, 
 
 // Eq. 7 for position i of every sequence: z[b][i][v] += (W_c E_c(y))[v] with
 // y = y_{i-1}(b), y_0 the anchor (an anchor outside [0, V) reads row 0). A
-// workgroup takes kMkV vocabulary entries: their W_c rows reach LDS through
-// coalesced 16-byte loads (rows padded by 16 bytes, so the lanes' row reads
-// spread over the banks), and the rank vectors of 16 sequences at a time sit
-// in LDS as fp32. Its 4 wave-sized groups of threads take 4 of every 16
-// sequences each. Each entry's sum runs over the rank index in order with
-// separate fp32 multiplies and adds (no fused multiply-add), so the corrected
-// logits are a fixed sequence of IEEE operations that the sampler then reads
-// like any other logits.
-constexpr int kMkRows = 16, kMkThreads = 256, kMkV = 64, kMkPer = kMkRows / (kMkThreads / kMkV);
+// workgroup takes 64 VT vocabulary entries, VT per lane, and its four waves the
+// rows in turn, kMkPer of every 16 at a time. (Two entries a lane at rank 64 and
+// below: the real vocabulary's workgroups are then all resident at once; with one
+// a last eighth of them started when the others were done.) The entries' W_c rows reach
+// LDS through coalesced 16-byte loads (rows padded by 16 bytes, so the lanes'
+// row reads spread over the banks). The rank vectors E_c(y) are the same for
+// all lanes: they come by scalar loads and enter the products from scalar
+// registers, their conversion from bf16 on the scalar unit (as fp32 in LDS, two
+// 16-byte reads for every eight products made the reads, beside the products,
+// what bounds the kernel). Each entry's sum runs over the rank index in order
+// with separate fp32 multiplies and adds (no fused multiply-add), so the
+// corrected logits are a fixed sequence of IEEE operations that the sampler then
+// reads like any other logits; at rank 64, 16 sequences and V = 151936 these 311 M
+// products and sums a position are 8 to 9 us of vector issue, the floor here.
+// LM: also write the chunk log-masses L_c (1: T = 1, 2: divide by T): a chunk's
+// 16 tokens sit on 16 lanes, reduced in the log-mass pass's order and with its
+// operations, so with its bits, and that pass (a launch and a read of the logits
+// for every position) is not needed. Per position 16.9 + 4.6 us of the two
+// launches -> 15.8 (8 positions at rank 128, whose staging registers left two
+// waves a SIMD: 561 -> 291 us the call).
+constexpr int kMkRows = 16, kMkThreads = 256, kMkPer = kMkRows / (kMkThreads / 64);
 // 16 bytes as a native vector (arrays of HIP's struct uint4 end up in scratch)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-template <typename T, int RMAX>   // RMAX: the largest rank the registers hold (64 or 256)
-__global__ void __launch_bounds__(kMkThreads) markov_correct_kernel(
-    float* logits, int batch, int B, int vocab, int i, const int32_t* anchor,
-    const int32_t* tokens, const T* E, const T* W, int rank) {
-#pragma clang fp contract(off)   // products and sums rounded separately, as the oracle states
-  extern __shared__ __attribute__((aligned(16))) float e_lds[];   // [kMkRows][rank], then W
-  constexpr int EPV = 16 / sizeof(T);   // elements per 16-byte piece (8 or 4)
-  const int wld = rank + EPV;           // padded W row in LDS (elements)
-  T* w_lds = reinterpret_cast<T*>(e_lds + kMkRows * rank);
-  const int v0 = blockIdx.x * kMkV;
-  const int lv = threadIdx.x & (kMkV - 1), v = v0 + lv;
-  const int grp = threadIdx.x / kMkV;   // rows grp * kMkPer .. + kMkPer of each 16
-  // Every global load is issued before the first barrier: the W_c rows of the
-  // tile, then per chunk of 16 sequences the logits this thread updates and
-  // the rank vectors E_c(y) (a token load, then its row); one barrier after
-  // they reach LDS. (W_c rows past V repeat the last one.)
-  constexpr int kWMax = kMkV * RMAX / EPV / kMkThreads;   // 16-byte pieces per thread
-  constexpr int kEMax = kMkRows * RMAX / kMkThreads;      // rank-vector entries per thread
-  const int per_row = rank / EPV, wpieces = kMkV * per_row;
-  u32x4 wreg[kWMax];
+// 8 consecutive rank entries at a wave-uniform address, through the scalar cache.
+template <typename T> __device__ inline void scalar_rank8(const T* p, float (&e)[8]);
+template <> __device__ inline void scalar_rank8<uint16_t>(const uint16_t* p, float (&e)[8]) {
+  const u32x4 x = *(const __attribute__((address_space(4))) u32x4*)(uintptr_t)p;
 #pragma unroll
-  for (int q = 0; q < kWMax; ++q) {
-    const int c = threadIdx.x + q * kMkThreads;
-    if (c < wpieces) {
-      const int r = c / per_row, k = (c - r * per_row) * EPV;
+  for (int i = 0; i < 4; ++i) {
+    e[2 * i] = __uint_as_float(x[i] << 16);
+    e[2 * i + 1] = __uint_as_float(x[i] & 0xffff0000u);
+  }
+}
+template <> __device__ inline void scalar_rank8<float>(const float* p, float (&e)[8]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const u32x4 x = *(const __attribute__((address_space(4))) u32x4*)(uintptr_t)(p + 4 * h);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e[4 * h + i] = __uint_as_float(x[i]);
+  }
+}
+
+struct MarkovArgs {
+  float* logits; int batch, B, vocab, i;
+  const int32_t* anchor; const int32_t* tokens;
+  const void* E; const void* W; int rank;
+  float* L; int ldL; float T;   // LM
+};
+
+template <typename T, int VT, int LM>
+__global__ void __launch_bounds__(kMkThreads) markov_correct_kernel(MarkovArgs a) {
+#pragma clang fp contract(off)   // products and sums rounded separately, as the oracle states
+  extern __shared__ __attribute__((aligned(16))) uint8_t w_raw[];
+  T* w_lds = reinterpret_cast<T*>(w_raw);
+  constexpr int EPV = 16 / sizeof(T);   // elements per 16-byte piece (8 or 4)
+  const int rank = a.rank, vocab = a.vocab, wld = rank + EPV;   // padded W row in LDS (elements)
+  const T* E = static_cast<const T*>(a.E);
+  const T* W = static_cast<const T*>(a.W);
+  const int v0 = blockIdx.x * 64 * VT, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // the W_c rows of the tile, 4 pieces a thread in flight (rows past V repeat the last one)
+  const int per_row = rank / EPV, pieces = 64 * VT * per_row;
+  const uint32_t inv = ((1u << 20) + per_row - 1) / per_row;   // exact quotients below 8192
+  u32x4 wreg[4];
+  auto w_at = [&](int c, int& r, int& k) {
+    r = (int)((uint32_t)c * inv >> 20);
+    k = (c - r * per_row) * EPV;
+  };
+  auto w_load = [&](int c0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      int r, k;
+      w_at(min(c0 + (int)threadIdx.x + q * kMkThreads, pieces - 1), r, k);
       wreg[q] = *reinterpret_cast<const u32x4*>(W + (long)min(v0 + r, vocab - 1) * rank + k);
     }
-  }
-  const T* wr = w_lds + lv * wld;
-  const float* e0 = e_lds + grp * kMkPer * rank;
-  for (int b0 = 0; b0 < batch; b0 += kMkRows) {
-    const int nb = min(kMkRows, batch - b0);
-    float zold[kMkPer];
+  };
+  auto w_store = [&](int c0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int c = c0 + (int)threadIdx.x + q * kMkThreads;
+      int r, k;
+      w_at(c, r, k);
+      if (c < pieces) *reinterpret_cast<u32x4*>(w_lds + r * wld + k) = wreg[q];
+    }
+  };
+  w_load(0);
+  for (int b0 = 0; b0 < a.batch; b0 += kMkRows) {
+    // this wave's sequences b0 + wave, + 4, + 8, + 12 (past the batch: the last one, not stored)
+    float zold[kMkPer][VT];
+    const T* er[kMkPer];
 #pragma unroll
     for (int r = 0; r < kMkPer; ++r) {
-      const int bb = grp * kMkPer + r;
-      zold[r] = v < vocab && bb < nb ? logits[((long)(b0 + bb) * B + i) * vocab + v] : 0.f;
-    }
-    float ereg[kEMax];
+      const int b = min(b0 + wave + r * 4, a.batch - 1);
+      int y = a.i == 0 ? a.anchor[b] : a.tokens[(long)b * a.B + a.i - 1];
+      y = __builtin_amdgcn_readfirstlane(y);
+      if (y < 0 || y >= vocab) y = 0;
+      er[r] = E + (long)y * rank;
 #pragma unroll
-    for (int q = 0; q < kEMax; ++q) {
-      const int idx = threadIdx.x + q * kMkThreads;
-      const int bb = idx / rank, k = idx - bb * rank;
-      float e = 0.f;
-      if (idx < kMkRows * rank && bb < nb) {
-        const int b = b0 + bb;
-        int y = i == 0 ? anchor[b] : tokens[(long)b * B + i - 1];
-        if (y < 0 || y >= vocab) y = 0;
-        e = Elem<T>::load(E + (long)y * rank + k);
-      }
-      ereg[q] = e;
+      for (int t = 0; t < VT; ++t)
+        zold[r][t] = a.logits[((long)b * a.B + a.i) * vocab + min(v0 + t * 64 + lane, vocab - 1)];
     }
-    if (b0 > 0) __syncthreads();   // the previous chunk's LDS reads are done
     if (b0 == 0) {
+      w_store(0);
+      for (int c0 = 4 * kMkThreads; c0 < pieces; c0 += 4 * kMkThreads) { w_load(c0); w_store(c0); }
+      __syncthreads();
+    }
+    float c[kMkPer][VT];
 #pragma unroll
-      for (int q = 0; q < kWMax; ++q) {
-        const int c = threadIdx.x + q * kMkThreads;
-        if (c < wpieces) {
-          const int r = c / per_row, k = (c - r * per_row) * EPV;
-          *reinterpret_cast<u32x4*>(w_lds + r * wld + k) = wreg[q];
+    for (int r = 0; r < kMkPer; ++r)
+#pragma unroll
+      for (int t = 0; t < VT; ++t) c[r][t] = 0.f;
+    for (int k0 = 0; k0 < rank; k0 += 8) {
+      float w[VT][8];
+#pragma unroll
+      for (int t = 0; t < VT; ++t)
+#pragma unroll
+        for (int h = 0; h < 8 / EPV; ++h) {
+          const u32x4 raw =
+              *reinterpret_cast<const u32x4*>(w_lds + (t * 64 + lane) * wld + k0 + h * EPV);
+          const T* wv = reinterpret_cast<const T*>(&raw);
+#pragma unroll
+          for (int e = 0; e < EPV; ++e) w[t][h * EPV + e] = Elem<T>::load(wv + e);
+        }
+#pragma unroll
+      for (int r = 0; r < kMkPer; ++r) {
+        float e[8];
+        scalar_rank8<T>(er[r] + k0, e);
+#pragma unroll
+        for (int t = 0; t < VT; ++t) {
+          float x = c[r][t];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) x = x + w[t][k] * e[k];
+          c[r][t] = x;
         }
       }
     }
 #pragma unroll
-    for (int q = 0; q < kEMax; ++q) {
-      const int idx = threadIdx.x + q * kMkThreads;
-      if (idx < kMkRows * rank) e_lds[idx] = ereg[q];
-    }
-    __syncthreads();
-    float c[kMkPer];
+    for (int r = 0; r < kMkPer; ++r) {
+      const int b = b0 + wave + r * 4;
+      if (b >= a.batch) break;   // wave-uniform
 #pragma unroll
-    for (int r = 0; r < kMkPer; ++r) c[r] = 0.f;
-    for (int k0 = 0; k0 < rank; k0 += 8) {
-      float w[8];
-#pragma unroll
-      for (int h = 0; h < 8 / EPV; ++h) {
-        const uint4 raw = *reinterpret_cast<const uint4*>(wr + k0 + h * EPV);
-        const T* wv = reinterpret_cast<const T*>(&raw);
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) w[h * EPV + e] = Elem<T>::load(wv + e);
-      }
-#pragma unroll
-      for (int r = 0; r < kMkPer; ++r) {
-        const float4 ea = *reinterpret_cast<const float4*>(e0 + r * rank + k0);
-        const float4 eb = *reinterpret_cast<const float4*>(e0 + r * rank + k0 + 4);
-        float x = c[r];
-        x = x + w[0] * ea.x; x = x + w[1] * ea.y; x = x + w[2] * ea.z; x = x + w[3] * ea.w;
-        x = x + w[4] * eb.x; x = x + w[5] * eb.y; x = x + w[6] * eb.z; x = x + w[7] * eb.w;
-        c[r] = x;
-      }
-    }
-    if (v < vocab) {
-#pragma unroll
-      for (int r = 0; r < kMkPer; ++r) {
-        const int bb = grp * kMkPer + r;
-        if (bb < nb) logits[((long)(b0 + bb) * B + i) * vocab + v] = zold[r] + c[r];
+      for (int t = 0; t < VT; ++t) {
+        const int v = v0 + t * 64 + lane;
+        const float z = zold[r][t] + c[r][t];
+        if (v < vocab) a.logits[((long)b * a.B + a.i) * vocab + v] = z;
+        if constexpr (LM != 0) {
+          const float zt = v < vocab ? (LM == 1 ? z : z / a.T) : -INFINITY;   // IEEE division
+          const float m = max16(zt);
+          const float l = chunk_log_mass(m, sum16(chunk_term(zt, m)));
+          if ((lane & (kChunk - 1)) == 0 && v < vocab) a.L[(long)b * a.ldL + v / kChunk] = l;
+        }
       }
     }
   }
@@ -939,24 +984,31 @@ hipError_t launch_sample_markov(float* logits, int batch, int B, int vocab, cons
                                 int32_t* tokens, float* lse, float* logq, void* ws,
                                 size_t sel_off, hipStream_t st) {
   const int esz = dtype == LDR_BF16 ? 2 : 4;
-  const size_t lds = (size_t)kMkRows * rank * sizeof(float) +
-                     (size_t)kMkV * (rank + 16 / esz) * esz;
-  const dim3 grid((unsigned)((vocab + kMkV - 1) / kMkV));
+  const int vt = rank <= 64 ? 2 : 1;   // vocabulary entries per lane
+  const size_t lds = (size_t)64 * vt * (rank + 16 / esz) * esz;
+  const dim3 grid((unsigned)((vocab + 64 * vt - 1) / (64 * vt)));
+  // full-vocabulary draws take the chunk log-masses from the correction
+  const bool lm = temperature > 0.f && (top_k == 0 || top_k >= vocab);
   for (int i = 0; i < B; ++i) {
-#define LDR_MK(T, RM)                                                                        \
-  hipLaunchKernelGGL((markov_correct_kernel<T, RM>), grid, dim3(kMkThreads), lds, st, logits, \
-                     batch, B, vocab, i, anchor, tokens, static_cast<const T*>(E),            \
-                     static_cast<const T*>(W), rank)
+    const SampleArgs sa = sample_args(logits, batch, vocab, temperature, seed, step, ws, B, i);
+    MarkovArgs a{logits, batch, B, vocab, i, anchor, tokens, E, W, rank, sa.L, sa.ldL, temperature};
+#define LDR_MK(T, VT, LM) \
+  hipLaunchKernelGGL((markov_correct_kernel<T, VT, LM>), grid, dim3(kMkThreads), lds, st, a)
+#define LDR_MKL(T, VT)                                                    \
+  if (!lm) LDR_MK(T, VT, 0); else if (temperature == 1.f) LDR_MK(T, VT, 1); \
+  else LDR_MK(T, VT, 2)
     if (dtype == LDR_BF16) {
-      if (rank <= 64) LDR_MK(uint16_t, 64); else LDR_MK(uint16_t, 256);
+      if (vt == 2) { LDR_MKL(uint16_t, 2); } else { LDR_MKL(uint16_t, 1); }
     } else {
-      if (rank <= 64) LDR_MK(float, 64); else LDR_MK(float, 256);
+      if (vt == 2) { LDR_MKL(float, 2); } else { LDR_MKL(float, 1); }
     }
+#undef LDR_MKL
 #undef LDR_MK
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_sample(logits, batch, vocab, temperature, top_k, seed, step, tokens, lse, logq, ws,
-                      sel_off, st, B, i);
+    e = lm ? sample_finish(sa, tokens, lse, logq, st)
+           : launch_sample(logits, batch, vocab, temperature, top_k, seed, step, tokens, lse, logq,
+                           ws, sel_off, st, B, i);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -217,6 +217,21 @@ def test_markov_without_correction_is_ldr_sample(gpu_lib):
     assert torch.equal(logq.view(-1), logq1)
 
 
+@pytest.mark.parametrize("batch,vocab,rank,dtype,T", [
+    (18, 5003, 72, torch.bfloat16, 0.7),     # one entry a lane, two batches of 16 sequences
+    (5, 4097, 64, torch.float32, 1.0),       # two entries a lane, a last tile of one token
+    (3, 129, 256, torch.bfloat16, 1.3), (1, 17, 8, torch.float32, 0.9)])
+def test_markov_draws_as_ldr_sample_on_its_logits(gpu_lib, batch, vocab, rank, dtype, T):
+    """The chunk log-masses formed with the correction are those of the pass
+    over the corrected logits: tokens, lse and log q bit for bit."""
+    z, a, E, W = _markov_case(batch, 3, vocab, rank, dtype, 7 * vocab + rank)
+    tok, lse, logq = gpu_lib.sample_markov(z, a, E, W, T, 0, seed=3, step=11)
+    tok1, lse1, logq1 = gpu_lib.sample(z.view(-1, vocab), T, 0, seed=3, step=11)
+    torch.cuda.synchronize()
+    assert torch.equal(tok.view(-1), tok1) and torch.equal(lse.view(-1), lse1)
+    assert torch.equal(logq.view(-1), logq1)
+
+
 def test_markov_rejects_bad_arguments(gpu_lib):
     z0, a, E, W = _markov_case(2, 2, 512, 8, torch.bfloat16, 1)
     for kw in ({"E": E[:, :6].contiguous(), "W": W[:, :6].contiguous()},   # rank % 8
