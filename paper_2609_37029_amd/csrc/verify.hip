@@ -10,19 +10,19 @@
 // bonus draw from p_{B+1}. r accepted candidates advance the prefix by r + 1,
 // which is the row count the next views update takes.
 //
-// Four launches at T > 0:
+// Three launches at T > 0:
 //  1. lse pass: one workgroup per (vocabulary chunk, candidate row) streams the
 //     B target rows of every sequence once (16-byte loads) and writes the
 //     chunk's running max and sum of exp(P / T);
-//  2. decide: one wave per sequence merges the lse partials, takes the
-//     in-order acceptance test (B exponentials) and writes r, r + 1 and the
-//     normalisers of the row where the round stops;
-//  3. emit pass: one workgroup per (sequence, vocabulary chunk) streams that
-//     target row (and draft row, 16-byte loads): Gumbel keys log w_v + g_v
-//     over the residual w = [p - q]_+ (every entry with w_v > 0 in fp32), and
+//  2. emit pass: one workgroup per (sequence, 2048 tokens). It first takes the
+//     in-order acceptance test itself (16 lanes merge a row's lse partials; a
+//     launch of its own for that is mostly the launch, and every workgroup's
+//     noise does not wait for it), then reads its part of the target row where
+//     the round stops (and of the draft row, 16-byte loads): Gumbel keys log w_v +
+//     g_v over the residual w = [p - q]_+ (every entry with w_v > 0 in fp32), and
 //     the bonus-rule keys fl(fl(P_v / T) + g_v) (the draw at a bonus, and the
 //     fallback when the residual has no positive mass);
-//  4. merge: the best key over the chunks, lower token first on ties.
+//  3. merge: the best key over the chunks, lower token first on ties.
 // T = 0 verifies greedily: pass 1 takes the first argmax of all B + 1 rows and
 // the merge compares them with the candidates.
 // A top-k proposal (the sampler's support, top_k > 0) has q = 0 outside the
@@ -43,7 +43,7 @@ constexpr int kInvalid = 0x7fffffff;
 
 struct LsePart { float m, s; int idx, pad; };     // max P / T, sum exp(P / T - m); argmax at T = 0
 struct EmitPart { float kr; int ir; float kb; int ib; };  // best residual key / bonus-rule key
-struct Decision { int stop; float plse, qlse; int pad; };  // where a sequence stops, its normalisers
+struct Decision { int stop; float plse; };   // where a sequence stops, the target row's normaliser
 
 __device__ inline bool better(float k1, int i1, float k2, int i2) {
   return k1 > k2 || (k1 == k2 && i1 < i2);
@@ -74,7 +74,6 @@ struct VerifyArgs {
   int chunk2, splits2;   // emit pass
   LsePart* lpart;        // [batch * rows][splits1]
   EmitPart* epart;       // [batch][splits2]
-  Decision* dec;         // [batch]
   int32_t* accepted; int32_t* token; int32_t* n_new;
 };
 
@@ -140,62 +139,75 @@ __global__ void __launch_bounds__(kThreads) verify_lse_kernel(VerifyArgs a) {
   }
 }
 
-// log-normaliser of candidate row i of sequence b from the lse partials
-__device__ inline float row_lse(const VerifyArgs& a, int b, int i) {
-  const LsePart* q = a.lpart + ((long)b * a.B + i) * a.splits1;
-  LsePart acc = q[0];
-  for (int s = 1; s < a.splits1; ++s) lse_combine(acc, q[s]);
-  return acc.m + logf(acc.s);
-}
-
-// Position where the round stops (B if every candidate passes), by the
-// acceptance test of Eq. 1 on the lanes of one wave, 64 candidates at a time.
-__device__ int stop_position(const VerifyArgs& a, int b) {
-  const int lane = threadIdx.x & 63;
-  for (int i0 = 0; i0 < a.B; i0 += 64) {
-    const int i = i0 + lane;
-    bool reject = false;
-    if (i < a.B) {
-      const int y = a.y[(long)b * a.B + i];
-      const float* zi = a.z + ((long)b * a.B + i) * a.V;
-      if (y < 0 || y >= a.V || (a.sel && !in_support(a.sel[(long)b * a.B + i], zi[y], y))) {
-        reject = true;   // q(y) = 0: the proposal cannot produce y
-      } else {
-        const float lp = a.P[((long)b * (a.B + 1) + i) * a.V + y] / a.T - row_lse(a, b, i);
-        const float lq = zi[y] / a.T - a.qlse[(long)b * a.B + i];
-        const float ratio = expf(lp - lq);
-        uint32_t w[4];
-        noise_block(noise_key(a.seed, a.step, 1), (uint32_t)b, (uint32_t)i, w);
-        reject = !(uniform_from_bits(w[0]) < ratio);
-      }
+// Position where the round of sequence b stops (B if every candidate passes), by
+// the acceptance test of Eq. 1, and the log-normaliser of the target row there.
+// A row of 16 lanes takes one candidate: it merges the row's lse partials (each
+// lane every sixteenth, then over the lanes: the max first, each sum rescaled
+// once) and tests it; kThreads / 16 candidates at a time, in order. Every thread
+// of the workgroup gets the result.
+__device__ Decision decide(const VerifyArgs& a, int b) {
+  constexpr int NC = kThreads / 16;
+  __shared__ int rejected[NC];
+  __shared__ float lse[NC];
+  const int c = (int)threadIdx.x >> 4, lr = (int)threadIdx.x & 15;
+  for (int i0 = 0; i0 < a.B; i0 += NC) {
+    const int i = min(i0 + c, a.B - 1);
+    const long row = (long)b * a.B + i;
+    const LsePart* q = a.lpart + row * a.splits1;
+    const int y = a.y[row];
+    const bool in = y >= 0 && y < a.V;
+    const float zy = a.z[row * a.V + (in ? y : 0)];
+    const float py = a.P[((long)b * (a.B + 1) + i) * a.V + (in ? y : 0)];
+    LsePart acc{-INFINITY, 0.f, kInvalid, 0};
+    for (int s = lr; s < a.splits1; s += 16) lse_combine(acc, q[s]);
+    const float m = max16(acc.m);
+    const float l = m + logf(sum16(m == -INFINITY ? 0.f : acc.s * __expf(acc.m - m)));
+    // q(y) = 0 outside the vocabulary or the support: the proposal cannot produce y
+    bool reject = !in || (a.sel && !in_support(a.sel[row], zy, y));
+    if (!reject) {
+      const float lp = py / a.T - l, lq = zy / a.T - a.qlse[row];
+      uint32_t w[4];
+      noise_block(noise_key(a.seed, a.step, 1), (uint32_t)b, (uint32_t)i, w);
+      reject = !(uniform_from_bits(w[0]) < expf(lp - lq));
     }
-    const uint64_t m = __ballot(reject);
-    if (m) return i0 + __ffsll((unsigned long long)m) - 1;
+    if (lr == 0) { rejected[c] = reject && i0 + c < a.B; lse[c] = l; }
+    __syncthreads();
+    for (int k = 0; k < NC; ++k)
+      if (rejected[k]) return Decision{i0 + k, lse[k]};   // the same on every thread
+    __syncthreads();
   }
-  return a.B;
+  return Decision{a.B, 0.f};
 }
 
-// One wave per sequence: the acceptance test, r and r + 1, and the
-// normalisers of the row where the round stops.
-__global__ void __launch_bounds__(64) verify_decide_kernel(VerifyArgs a) {
-  const int b = blockIdx.x;
-  const int stop = stop_position(a, b);
-  if (threadIdx.x == 0) {
-    Decision d{stop, 0.f, 0.f, 0};
-    if (stop < a.B) { d.plse = row_lse(a, b, stop); d.qlse = a.qlse[(long)b * a.B + stop]; }
-    a.dec[b] = d;
-    a.accepted[b] = stop;
-    a.n_new[b] = stop + 1;
+__device__ inline float max64(float v) {
+  v = max16(v);
+  v = fmaxf(v, __shfl_xor(v, 16));
+  return fmaxf(v, __shfl_xor(v, 32));
+}
+// Over the wave: each kind's best key and the lowest token among its equals.
+__device__ inline EmitPart best_of_wave(const EmitPart& e) {
+  EmitPart o{max64(e.kr), 0, max64(e.kb), 0};
+  int ir = e.kr == o.kr ? e.ir : kInvalid, ib = e.kb == o.kb ? e.ib : kInvalid;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    ir = min(ir, __shfl_xor(ir, off));
+    ib = min(ib, __shfl_xor(ib, off));
   }
+  o.ir = ir; o.ib = ib;
+  return o;
 }
 
 template <bool UNIT_T, bool VEC>
 __global__ void __launch_bounds__(kThreads) verify_emit_kernel(VerifyArgs a) {
   const int b = blockIdx.x, sp = blockIdx.y;
-  const Decision d = a.dec[b];
+  const Decision d = decide(a, b);
   const int stop = d.stop;
+  if (sp == 0 && threadIdx.x == 0) {
+    a.accepted[b] = stop;
+    a.n_new[b] = stop + 1;
+  }
   const bool residual = stop < a.B;
-  const float plse = d.plse, qlse = d.qlse;
+  const float plse = d.plse, qlse = residual ? a.qlse[(long)b * a.B + stop] : 0.f;
   const float* p = a.P + ((long)b * (a.B + 1) + stop) * a.V;
   const float* z = residual ? a.z + ((long)b * a.B + stop) * a.V : nullptr;
   const TopK sel = residual && a.sel ? a.sel[(long)b * a.B + stop] : TopK{0u, -1};
@@ -265,11 +277,7 @@ __global__ void __launch_bounds__(kThreads) verify_emit_kernel(VerifyArgs a) {
         if (k == km) { zkm = zr[k]; wkm = bits[k]; }
       exact(vb + km, pt[km], zkm, wkm, true, residual);
     }
-    float tb = e.kb, tr = e.kr;
-    for (int off = 32; off >= 1; off >>= 1) {
-      tb = fmaxf(tb, __shfl_xor(tb, off));
-      tr = fmaxf(tr, __shfl_xor(tr, off));
-    }
+    const float tb = max64(e.kb), tr = max64(e.kr);
 #pragma unroll
     for (int k = 0; k < kGroup; ++k) {
       const int v = vb + k;
@@ -281,12 +289,7 @@ __global__ void __launch_bounds__(kThreads) verify_emit_kernel(VerifyArgs a) {
       if (need_b || need_r) exact(v, pt[k], zr[k], bits[k], need_b, need_r);
     }
   }
-  for (int off = 32; off >= 1; off >>= 1) {
-    const EmitPart o{__shfl_xor(e.kr, off), __shfl_xor(e.ir, off), __shfl_xor(e.kb, off),
-                     __shfl_xor(e.ib, off)};
-    if (better(o.kr, o.ir, e.kr, e.ir)) { e.kr = o.kr; e.ir = o.ir; }
-    if (better(o.kb, o.ib, e.kb, e.ib)) { e.kb = o.kb; e.ib = o.ib; }
-  }
+  e = best_of_wave(e);
   __shared__ EmitPart red[kThreads / 64];
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
   __syncthreads();
@@ -308,12 +311,7 @@ __global__ void __launch_bounds__(64) verify_merge_kernel(VerifyArgs a) {
     if (better(o.kr, o.ir, e.kr, e.ir)) { e.kr = o.kr; e.ir = o.ir; }
     if (better(o.kb, o.ib, e.kb, e.ib)) { e.kb = o.kb; e.ib = o.ib; }
   }
-  for (int off = 32; off >= 1; off >>= 1) {
-    const EmitPart o{__shfl_xor(e.kr, off), __shfl_xor(e.ir, off), __shfl_xor(e.kb, off),
-                     __shfl_xor(e.ib, off)};
-    if (better(o.kr, o.ir, e.kr, e.ir)) { e.kr = o.kr; e.ir = o.ir; }
-    if (better(o.kb, o.ib, e.kb, e.ib)) { e.kb = o.kb; e.ib = o.ib; }
-  }
+  e = best_of_wave(e);
   // a residual without positive mass (or a bonus) takes the bonus-rule draw
   if (threadIdx.x == 0) a.token[b] = e.ir != kInvalid ? e.ir : e.ib;
 }
@@ -361,9 +359,12 @@ Plan make_plan(int batch, int B, int V, bool greedy) {
   s1 = s1 < 1 ? 1 : (s1 > max1 ? max1 : s1);
   p.chunk1 = ((V + s1 - 1) / s1 + sweep1 - 1) / sweep1 * sweep1;
   p.splits1 = (V + p.chunk1 - 1) / p.chunk1;
-  // emit pass: about 512 workgroups, chunks of whole Philox sweeps
+  // emit pass: one sweep of kThreads x 8 tokens a workgroup up to about 2048
+  // workgroups (8 a CU, all resident), whole sweeps beyond. (16 sequences: 25
+  // workgroups each of three sweeps, one waiting for the other, and a decision
+  // launch before them took 16.4 + 4.7 us, 75 of one sweep 15.1 with the decision.)
   const int sweep2 = kGroup * kThreads;
-  int s2 = batch >= 512 ? 1 : 512 / batch;
+  int s2 = batch >= 2048 ? 1 : 2048 / batch;
   const int max2 = (V + sweep2 - 1) / sweep2;
   s2 = s2 < 1 ? 1 : (s2 > max2 ? max2 : s2);
   p.chunk2 = ((V + s2 - 1) / s2 + sweep2 - 1) / sweep2 * sweep2;
@@ -378,7 +379,7 @@ size_t verify_workspace_bytes(int batch, int B, int V) {
   const size_t l1 = (size_t)batch * (B + 1) * g.splits1, l2 = (size_t)batch * B * t.splits1;
   const size_t lse = align_up((l1 > l2 ? l1 : l2) * sizeof(LsePart));
   return lse + align_up((size_t)batch * t.splits2 * sizeof(EmitPart)) +
-         align_up(batch * sizeof(Decision)) + (size_t)batch * B * sizeof(TopK);
+         (size_t)batch * B * sizeof(TopK);
 }
 
 hipError_t launch_verify(const float* P, const float* z, const int32_t* y, const float* qlse,
@@ -396,13 +397,12 @@ hipError_t launch_verify(const float* P, const float* z, const int32_t* y, const
   a.lpart = static_cast<LsePart*>(ws);
   a.epart = reinterpret_cast<EmitPart*>(static_cast<uint8_t*>(ws) +
                                         align_up((l1 > l2 ? l1 : l2) * sizeof(LsePart)));
-  a.dec = reinterpret_cast<Decision*>(reinterpret_cast<uint8_t*>(a.epart) +
-                                      align_up((size_t)batch * pl.splits2 * sizeof(EmitPart)));
   a.accepted = accepted; a.token = token; a.n_new = n_new;
   a.sel = nullptr;
   if (!greedy && top_k > 0 && top_k < V && B > 0) {   // the draft rows' top-k supports
-    TopK* sel = reinterpret_cast<TopK*>(reinterpret_cast<uint8_t*>(a.dec) +
-                                        align_up(batch * sizeof(Decision)));
+    TopK* sel = reinterpret_cast<TopK*>(
+        reinterpret_cast<uint8_t*>(a.epart) +
+        align_up((size_t)batch * pl.splits2 * sizeof(EmitPart)));
     const hipError_t e = launch_topk_select(z, batch * B, V, top_k, sel, st);
     if (e != hipSuccess) return e;
     a.sel = sel;
@@ -426,9 +426,7 @@ hipError_t launch_verify(const float* P, const float* z, const int32_t* y, const
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(verify_decide_kernel, dim3(batch), dim3(64), 0, st, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
   const dim3 g2(batch, pl.splits2);
   if (T == 1.f) {
     if (vec) hipLaunchKernelGGL((verify_emit_kernel<true, true>), g2, dim3(kThreads), 0, st, a);
