@@ -940,30 +940,25 @@ GemmPlan plan_gemm(int dtype, int M, int N, int K, bool allow_split, bool swiglu
     }
   } else {
     // 128, 96 or 64 columns and a K split that keeps the workgroups within one
-    // round over the CUs (no split where the tiles alone take more). Taken in
-    // order: the plan whose workgroups fill the most of their last round; then
-    // one whose K range is at most 2048 (longer ranges measured slower, each
-    // workgroup re-reading more activation rows); then the fewest splits (the
-    // fp32 partial tiles are written in a burst at the end and read back by
-    // the next kernel); then the fewest bytes per workgroup.
-    double best_u = -1.0, best_v = 0.0;
-    bool best_short = false;
+    // round over the CUs (no split where the tiles alone take more): the least
+    // rounds over the CUs times the bytes a workgroup moves, its activation rows
+    // and weight columns over its K range, and four times its output tile (fp32
+    // partials are written in a burst at the end and read back by the next
+    // kernel). At 1024 rows the down projection then runs on 128 columns split
+    // in two instead of 64 unsplit, with as many workgroups (120 -> 84 us); at 256
+    // rows QKV, O and down keep 96 x 4, 64 x 4 and 128 x 8 (O at 128 x 8, the next
+    // by this cost, makes its own time up in the norm that reads the partials).
+    double best = 0.0;
     for (const int w : widths) {
       const long tiles = (long)((N + w - 1) / w) * p.grid_y;
       for (int sp = 1; sp <= max_splits; sp *= 2) {
         if (K % (sp * BK) != 0 || K / sp < 2 * BK) break;
         const long wg = tiles * sp;
         if (sp > 1 && wg > kCUs) break;
-        const double u = (double)wg / (double)(((wg + kCUs - 1) / kCUs) * kCUs);
-        const bool shrt = K / sp <= 2048;
-        const double vol = ((double)p.bm + w) * (K / sp) * 2.0;
-        bool take;
-        if (u > best_u + 1e-9) take = true;
-        else if (u < best_u - 1e-9) take = false;
-        else if (shrt != best_short) take = shrt;
-        else if (sp != p.splits) take = sp < p.splits;
-        else take = vol < best_v;
-        if (take) { best_u = u; best_v = vol; best_short = shrt; p.bn = w; p.splits = sp; }
+        const double rounds = (double)((wg + kCUs - 1) / kCUs);
+        const double cost =
+            rounds * (((double)p.bm + w) * (K / sp) * 2.0 + 4.0 * p.bm * w * 4.0 * (sp > 1 ? 2 : 1));
+        if (best == 0.0 || cost < best) { best = cost; p.bn = w; p.splits = sp; }
       }
     }
   }
