@@ -143,8 +143,9 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, int n0, int m0, in
 // linear ids are renumbered so that XCD c takes the c-th eighth of the tiles
 // in (z, x, y) order. A K split's activation columns are then read into one
 // or two XCDs' L2 instead of all eight, and the row tiles of one column tile
-// (M above one tile) share their weight columns in one L2.
-__device__ __forceinline__ void xcd_tile(int& x, int& y, int& z) {
+// (M above one tile) share their weight columns in one L2. Returns l, the tile's
+// place in that order.
+__device__ __forceinline__ int xcd_tile(int& x, int& y, int& z) {
   const int gx = gridDim.x, gy = gridDim.y;
   const int total = gx * gy * gridDim.z;
   const int lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
@@ -153,6 +154,7 @@ __device__ __forceinline__ void xcd_tile(int& x, int& y, int& z) {
   y = l % gy;
   x = (l / gy) % gx;
   z = l / (gx * gy);
+  return l;
 }
 
 // fp32 on v_mfma_f32_16x16x4_f32 (full fp32 products and sums). A workgroup
@@ -326,9 +328,24 @@ __device__ __forceinline__ void frag_gemm(const GemmArgs& a) {
   __shared__ __attribute__((aligned(1024))) uint8_t Wsm[NB * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int bx, by, z;
-  xcd_tile(bx, by, z);
+  const int l = xcd_tile(bx, by, z);
   const int n0 = bx * BN, m0 = by * BM;
   const int kper = a.K / a.splits, kbeg = z * kper, nk = kper / BK;
+  // Workgroups start their K range at different steps and wrap around: weight
+  // rows lie a power of two apart, so workgroups that walk K in step keep asking
+  // for the same 128 bytes of every row, which sit on few of the memory
+  // channels. Up to 64 rows, coarse phases by groups of 8 tiles and finer ones
+  // inside (the batch-1
+  // SwiGLU GEMM 45 -> 35 us, 4.5 -> 5.7 TB/s; steps of 16 and 64 rows 825 -> 770 and
+  // 925 -> 858 us); above, coarse phases by XCD, finer ones inside it, so that the
+  // workgroups of one L2 stay near the same activation columns (256 rows 1211 ->
+  // 1175 us, 1024 rows unchanged; the first rule costs those 3%).
+  const int lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+  const int rot = (BM <= 64 ? ((l >> 3) & 7) * 8 + (l & 7) : (lin & 7) * 8 + ((l >> 3) & 7)) * nk / 64;
+  auto kstep = [&](int st) {   // the K step of stage st (past the end: the last one's)
+    const int q = min(st, nk - 1) + rot;
+    return q >= nk ? q - nk : q;
+  };
   if (wave >= NW) {
     // loader l: groups l * GPL .. + GPL of every stage; lane -> row g * 8 +
     // lane / 8, physical chunk lane % 8 <- logical chunk (lane % 8) ^ (row & 7);
@@ -348,7 +365,7 @@ __device__ __forceinline__ void frag_gemm(const GemmArgs& a) {
       wdst[q] = g * 1024;
     }
     auto issue_w = [&](int buf, int stage) {   // stages past the end reload the last one
-      const int off = min(stage, nk - 1) * BK;
+      const int off = kstep(stage) * BK;
       uint8_t* dst = Wsm + buf * STAGE;
 #pragma unroll
       for (int q = 0; q < GPL; ++q)
@@ -391,7 +408,7 @@ __device__ __forceinline__ void frag_gemm(const GemmArgs& a) {
   constexpr long STA = ROWA ? BK : 1024;     // elements between steps
   u32x4 aq[FRA][MTW][2];
   auto load_a = [&](u32x4 (&dst)[MTW][2], int stage) {   // past the end: the last stage again
-    const long off = (long)min(stage, nk - 1) * STA;
+    const long off = (long)kstep(stage) * STA;
 #pragma unroll
     for (int i = 0; i < MTW; ++i)
 #pragma unroll
