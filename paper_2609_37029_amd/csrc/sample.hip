@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(kSelThreads) topk_chunks_kernel(SampleArgs a, 
   {  // 1. chunk maxima: 4 lanes hold a chunk, 4 tokens each
     constexpr int U = 4, kSweep = kSelThreads * 4;
     auto load = [&](int v, float (&x)[4]) {
-      if (VEC && v + 4 <= V) {
+      if constexpr (VEC) {   // V % 4 == 0, v at most V - 4
         const float4 t = *reinterpret_cast<const float4*>(z + v);
         x[0] = t.x; x[1] = t.y; x[2] = t.z; x[3] = t.w;
       } else {

@@ -322,7 +322,7 @@ __global__ void __launch_bounds__(kThreads) views_update_kernel(UpdateArgs a) {
 // Long updates of few sequences (prefill) leave most CUs without work at one
 // workgroup per (group, layer, sequence), so the rows are then also cut into
 // `splits` ranges of whole tiles: each workgroup writes its (m, l, O) to the
-// handle's scratch and views_merge_kernel combines them in order.
+// handle's scratch and views_commit_merge_kernel combines them in order.
 //
 // What bounds it: the rows' stream from HBM once the loads run ahead of the
 // tiles. Qwen3-8B shape, a 4096-row chunk
@@ -594,7 +594,8 @@ __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
 
 template <int DH, int NW, int NB, bool SUM>
 __global__ void __launch_bounds__((NB > 1 ? NW + 1 : NW) * 64)
-    __attribute__((amdgpu_waves_per_eu(NB > 1 ? 4 : 3))) views_rows_kernel(UpdateArgs a) {
+    __attribute__((amdgpu_waves_per_eu(NB > 1 ? 4 : 3)))
+views_update_rows_kernel(UpdateArgs a) {
   views_rows_body<DH, NW, NB, SUM>(a);
   commit_tail(a.ct, blockIdx.z / a.splits);
 }
@@ -604,7 +605,7 @@ __global__ void __launch_bounds__((NB > 1 ? NW + 1 : NW) * 64)
 // layer, query tile, sequence); a thread owns 4 dims of one query, the threads
 // of a query in one wave (so every one of them has read eta before one of them writes it).
 template <int DH>
-__global__ void __launch_bounds__(256) views_merge_kernel(UpdateArgs a) {
+__global__ void __launch_bounds__(256) views_commit_merge_kernel(UpdateArgs a) {
   constexpr int C4 = DH / 4, QP = 256 / C4, U = 8;   // float4s a query, queries, ranges in flight
   const int g = blockIdx.x % a.hkv, j = blockIdx.x / a.hkv, b = blockIdx.z;
   const int n = a.n_new[b], nq = a.rep * a.R;
@@ -827,8 +828,8 @@ template <int NB, bool SUM>
 hipError_t launch_rows(const Shape& s, const UpdateArgs& a, dim3 grid, hipStream_t st) {
 #define LDR_VU(DH, NW)                                                                        \
   if (s.d == DH && views_rows_waves(s) == NW) {                                               \
-    hipLaunchKernelGGL((views_rows_kernel<DH, NW, NB, SUM>), grid, dim3((NB > 1 ? NW + 1 : NW) * 64), \
-                       0, st, a);                                                             \
+    hipLaunchKernelGGL((views_update_rows_kernel<DH, NW, NB, SUM>), grid,                     \
+                       dim3((NB > 1 ? NW + 1 : NW) * 64), 0, st, a);                          \
     return hipGetLastError();                                                                 \
   }
   LDR_VU(128, 4) LDR_VU(64, 4)
@@ -918,8 +919,8 @@ hipError_t launch_views_update(const Shape& s, const Layout& L, int batch, void*
       if (e != hipSuccess) return e;
       a.ct = ct;
       const dim3 mgrid(s.hkv * s.D, q / (1024 / s.d), batch);
-      if (s.d == 128) hipLaunchKernelGGL(views_merge_kernel<128>, mgrid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL(views_merge_kernel<64>, mgrid, dim3(256), 0, st, a);
+      if (s.d == 128) hipLaunchKernelGGL(views_commit_merge_kernel<128>, mgrid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL(views_commit_merge_kernel<64>, mgrid, dim3(256), 0, st, a);
       return hipGetLastError();
     }
   } else if (rows_kernel) {
