@@ -335,13 +335,14 @@ __device__ __forceinline__ void frag_gemm(const GemmArgs& a) {
   // rows lie a power of two apart, so workgroups that walk K in step keep asking
   // for the same 128 bytes of every row, which sit on few of the memory
   // channels. Up to 64 rows, coarse phases by groups of 8 tiles and finer ones
-  // inside (the batch-1
-  // SwiGLU GEMM 45 -> 35 us, 4.5 -> 5.7 TB/s; steps of 16 and 64 rows 825 -> 770 and
-  // 925 -> 858 us); above, coarse phases by XCD, finer ones inside it, so that the
-  // workgroups of one L2 stay near the same activation columns (256 rows 1211 ->
-  // 1175 us, 1024 rows unchanged; the first rule costs those 3%).
+  // inside (the batch-1 SwiGLU GEMM 45 -> 35 us, 4.5 -> 5.7 TB/s; steps of 16 and
+  // 64 rows 825 -> 770 and 925 -> 858 us); above, coarse phases by XCD, finer ones
+  // inside it, so that the workgroups of one L2 stay near the same activation
+  // columns (256 rows 1211 -> 1175 us, 1024 rows unchanged; the first rule costs
+  // those 3%).
   const int lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-  const int rot = (BM <= 64 ? ((l >> 3) & 7) * 8 + (l & 7) : (lin & 7) * 8 + ((l >> 3) & 7)) * nk / 64;
+  const int phase = BM <= 64 ? ((l >> 3) & 7) * 8 + (l & 7) : (lin & 7) * 8 + ((l >> 3) & 7);
+  const int rot = phase * nk / 64;
   auto kstep = [&](int st) {   // the K step of stage st (past the end: the last one's)
     const int q = min(st, nk - 1) + rot;
     return q >= nk ? q - nk : q;

@@ -226,17 +226,17 @@ __device__ __forceinline__ void views_update_body(const UpdateArgs& a) {
     float tmax = -INFINITY;
 #pragma unroll
     for (int r = 0; r < kTileRows; ++r) {
-      float p = 0.f;
-      if (r < nr) {
+      s[r] = -INFINITY;
+      if (r < nr) {   // uniform: a step's few rows skip the rest of the tile (9: 8.5 -> 7.1 us)
+        float p = 0.f;
 #pragma unroll
         for (int c = 0; c < NV; ++c) {
           const float4 k4 = *reinterpret_cast<const float4*>(&Ks[r][(c * tpq + part) * 4]);
           p += gq[c * 4 + 0] * k4.x + gq[c * 4 + 1] * k4.y + gq[c * 4 + 2] * k4.z +
                gq[c * 4 + 3] * k4.w;
         }
+        s[r] = group_sum(p, tpq);
       }
-      p = group_sum(p, tpq);
-      s[r] = r < nr ? p : -INFINITY;
       tmax = fmaxf(tmax, s[r]);
     }
     const float nm = fmaxf(mx, tmax);
@@ -483,6 +483,7 @@ __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
     if constexpr (NB == 1) wait_vmcnt<0>();   // own share of the tile
     else __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));   // own LDS reads of stage kt - 1
     __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");   // the tile's LDS reads stay behind the barrier
     __builtin_amdgcn_sched_barrier(0);
     uint8_t* Kt = sm + buf * STAGE;
     uint8_t* Vt = Kt + MAT;
