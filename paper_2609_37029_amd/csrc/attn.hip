@@ -418,6 +418,14 @@ __global__ void __launch_bounds__(64 * HPW * NSEG) attention_mfma_kernel(AttnArg
     pv(sc, vbuf);
   };
 
+  // A chunk of the region. One without a valid row (a pooled bank that is not
+  // full yet) is left out: as a segment's first it would set m = -inf as the
+  // reference of its scores, and exp(-inf - -inf) is NaN.
+  auto chunk_item = [&](int chunk) {
+    const int nvalid = chunk_valid(chunk);   // the same on every lane
+    if (nvalid > 0) item(Ks, Vt, nvalid);
+  };
+
   // ---- first items, on rows already in LDS: the block (segment 0) and the
   // summary (last segment: G rows as keys, M^T as values, keys R .. 31 masked)
   if (seg == 0) item(Blk, Blk + KTILE, B);
@@ -449,7 +457,7 @@ __global__ void __launch_bounds__(64 * HPW * NSEG) attention_mfma_kernel(AttnArg
         if (it < steps) {
           LDR_STASH(it)
           lds_barrier();
-          if (it < items) item(Ks, Vt, chunk_valid(cbeg + it));
+          if (it < items) chunk_item(cbeg + it);
           lds_barrier();
         }
       }
@@ -464,7 +472,7 @@ __global__ void __launch_bounds__(64 * HPW * NSEG) attention_mfma_kernel(AttnArg
             // waits stay exact; past the segment's end it repeats its last chunk)
             LDR_FETCH(j, min(cbeg + it + WD, cend - 1))
             lds_barrier();
-            if (it < items) item(Ks, Vt, chunk_valid(cbeg + it));
+            if (it < items) chunk_item(cbeg + it);
             lds_barrier();
           }
         }

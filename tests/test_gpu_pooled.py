@@ -54,6 +54,13 @@ def test_pooled_bf16_mfma(gpu_lib, prefix, chunk):
     run(gpu_lib, MINI_BF16_POOLED, 3, prefix, chunk)
 
 
+@pytest.mark.parametrize("slots,prefix", [(32, 0), (128, 0), (128, 5), (128, 70), (128, 300)])
+def test_pooled_chunks_without_a_valid_row(gpu_lib, slots, prefix):
+    """Banks that are not full: key segments of the attention (two at 32 slots,
+    four at 128) whose first 32-row chunk, or every chunk, holds no valid row."""
+    run(gpu_lib, MINI_BF16_POOLED.replace(pool_slots=slots), 2, prefix, 128, decode=0)
+
+
 def test_pooled_without_the_window(gpu_lib):
     run(gpu_lib, MINI_BF16_POOLED.replace(drop_views=1), 2, 200, 90)
 
