@@ -143,9 +143,11 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, int n0, int m0, in
 // linear ids are renumbered so that XCD c takes the c-th eighth of the tiles
 // in (z, x, y) order. A K split's activation columns are then read into one
 // or two XCDs' L2 instead of all eight, and the row tiles of one column tile
-// (M above one tile) share their weight columns in one L2. Returns l, the tile's
-// place in that order.
-__device__ __forceinline__ int xcd_tile(int& x, int& y, int& z) {
+// (M above one tile) share their weight columns in one L2. Returns the place in
+// that order, and the XCD, of the first row tile of this column tile and split:
+// the same for all of its row tiles.
+struct ColumnPlace { int l, xcd; };
+__device__ __forceinline__ ColumnPlace xcd_tile(int& x, int& y, int& z) {
   const int gx = gridDim.x, gy = gridDim.y;
   const int total = gx * gy * gridDim.z;
   const int lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
@@ -154,7 +156,11 @@ __device__ __forceinline__ int xcd_tile(int& x, int& y, int& z) {
   y = l % gy;
   x = (l / gy) % gx;
   z = l / (gx * gy);
-  return l;
+  // the XCD of place l - y (the inverse of l above): this one's own for the first row tile
+  const int l0 = l - y, cut = r * (q + 1);
+  int xcd = c;
+  if (y > 0) xcd = l0 < cut ? l0 / (q + 1) : r + (l0 - cut) / q;
+  return ColumnPlace{l0, xcd};
 }
 
 // fp32 on v_mfma_f32_16x16x4_f32 (full fp32 products and sums). A workgroup
@@ -328,7 +334,7 @@ __device__ __forceinline__ void frag_gemm(const GemmArgs& a) {
   __shared__ __attribute__((aligned(1024))) uint8_t Wsm[NB * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int bx, by, z;
-  const int l = xcd_tile(bx, by, z);
+  const ColumnPlace cp = xcd_tile(bx, by, z);
   const int n0 = bx * BN, m0 = by * BM;
   const int kper = a.K / a.splits, kbeg = z * kper, nk = kper / BK;
   // Workgroups start their K range at different steps and wrap around: weight
@@ -340,8 +346,10 @@ __device__ __forceinline__ void frag_gemm(const GemmArgs& a) {
   // inside it, so that the workgroups of one L2 stay near the same activation
   // columns (256 rows 1211 -> 1175 us, 1024 rows unchanged; the first rule costs
   // those 3%).
-  const int lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-  const int phase = BM <= 64 ? ((l >> 3) & 7) * 8 + (l & 7) : (lin & 7) * 8 + ((l >> 3) & 7);
+  // All row tiles of a column tile start at the same step, whatever their number:
+  // they read the same weights side by side, and a sequence's logits do not
+  // depend on the row tile it falls in.
+  const int phase = BM <= 64 ? ((cp.l >> 3) & 7) * 8 + (cp.l & 7) : cp.xcd * 8 + ((cp.l >> 3) & 7);
   const int rot = phase * nk / 64;
   auto kstep = [&](int st) {   // the K step of stage st (past the end: the last one's)
     const int q = min(st, nk - 1) + rot;

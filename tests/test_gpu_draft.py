@@ -76,6 +76,21 @@ def test_row_tiles_match_oracle(gpu_lib, batch, block):
         check_logits(zc[b], ref[b], s)
 
 
+# 3, 5 and 7 row tiles of 256: numbers that do not divide the tiles of an XCD
+@pytest.mark.parametrize("batch", [40, 70, 100])
+def test_identical_sequences_have_identical_logits(gpu_lib, batch):
+    """The row tile a sequence falls in does not change the order of its sums."""
+    s = MINI_BF16
+    v = gpu_lib.Views(s, batch, synth.make_G(s, device="cuda")).init()
+    K, V, h = (x[:1].expand(batch, *x.shape[1:]).contiguous()
+               for x in synth.decode_rows(s, 1, 90, 0, device="cuda"))
+    v.update(torch.full((batch,), 90, dtype=torch.int32, device="cuda"), K, V, h)
+    dw = gpu_lib.DraftWeights(synth.make_weights(s, gain_std=0.1, device="cuda"))
+    z = gpu_lib.draft_step(v, dw, torch.full((batch,), 7, dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    assert torch.equal(z, z[:1].expand_as(z))
+
+
 # fp32: one and two row tiles of 16 with remainders, ragged and paired column
 # tiles, a window whose rows do not start on 16 bytes, grouped heads of 128,
 # K split over workgroups (mlp 2048)
