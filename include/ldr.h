@@ -182,10 +182,7 @@ int ldr_config_check(const ldr_config* cfg);
  *   h_boundary dev [batch][L_b][hidden] dtype: boundary states after it (may be
  *              NULL with LDR_DROP_BOUNDARY)
  * The handle also owns a small device status block (the sticky flags and the
- * update's commit counters, 64 bytes per sequence) and, where its sequences are few (learned
- * summary, bf16), scratch for the partial statistics of long updates (17 MB for
- * one sequence of the Qwen3-8B shape; without room for it updates still run,
- * less spread over the GPU), both freed by ldr_views_destroy. */
+ * update's commit counters, 64 bytes per sequence), freed by ldr_views_destroy. */
 int ldr_views_init(ldr_views** out, const ldr_config* cfg, int32_t batch, void* arena,
                    int64_t* pos, const void* G, const int32_t* n_prefix, int32_t max_prefix,
                    const void* K_prefix, const void* V_prefix, const void* h_boundary,
@@ -218,6 +215,25 @@ int ldr_views_init(ldr_views** out, const ldr_config* cfg, int32_t batch, void* 
  *   h_new       dev [batch][L_b][hidden] dtype (may be NULL with LDR_DROP_BOUNDARY) */
 int ldr_views_update(ldr_views* v, const int32_t* n_new, int32_t max_new, const void* K_new,
                      const void* V_new, const void* h_new, void* stream);
+
+/* Workspace bytes with which ldr_views_update_ws spreads an update of up to
+ * max_new rows over the GPU: ranges * batch * D * Hq * R * (d + 2) * 4 bytes
+ * (learned summary, bf16) for an update of 256 rows or more whose D * Hkv *
+ * batch workgroups would leave the GPU idle, cut into up to 32 row ranges of at
+ * least 128 rows; 0 where it is not cut. 16 MB (12 ranges) for 4096 rows of one
+ * sequence of the Qwen3-8B shape. 0 for an invalid configuration or size. */
+size_t ldr_views_update_workspace_bytes(const ldr_config* cfg, int32_t batch, int32_t max_new);
+
+/* ldr_views_update with a workspace for the partial statistics of the row
+ * ranges of a long update. The same views as without it but for the order of
+ * the summary's fp32 sums.
+ *   workspace   dev, ldr_views_update_workspace_bytes(cfg, batch, max_new) bytes,
+ *               16-byte aligned, free again when the stream has passed the
+ *               update; or NULL: ldr_views_update. LDR_EINVAL if short or
+ *               misaligned. */
+int ldr_views_update_ws(ldr_views* v, const int32_t* n_new, int32_t max_new, const void* K_new,
+                        const void* V_new, const void* h_new, void* workspace,
+                        size_t workspace_bytes, void* stream);
 
 /* Waits for `stream` and returns the sticky device status: LDR_OK,
  * LDR_ERANGE once any update saw an out-of-range row count, else LDR_EINVAL

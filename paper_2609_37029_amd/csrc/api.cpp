@@ -137,8 +137,6 @@ struct ldr_views {
   const void* G;
   int32_t* status;  // device: the sticky flags, and from word kCommitCounter the
                     // update's commit counters
-  void* scratch;    // device: partial statistics of long updates (behind the status
-                    // block, one allocation), or null
 };
 
 extern "C" {
@@ -204,8 +202,11 @@ const char* ldr_strerror(int status) {
 
 static int views_update_impl(ldr_views* v, const int32_t* n_new, int32_t max_new,
                              const void* K_new, const void* V_new, const void* h_new,
-                             hipStream_t st) {
+                             void* workspace, size_t workspace_bytes, hipStream_t st) {
   if (!v || !n_new || max_new < 0) return LDR_EINVAL;
+  if (workspace && (!aligned(workspace, 16) ||
+                    workspace_bytes < views_update_ws_bytes(v->s, v->batch, max_new)))
+    return LDR_EINVAL;
   if (max_new > 0 && (!K_new || !V_new || !aligned(K_new, 16) || !aligned(V_new, 16)))
     return LDR_EINVAL;
   if (v->s.keep_bnd && (!h_new || !aligned(h_new, 16))) return LDR_EINVAL;
@@ -214,7 +215,7 @@ static int views_update_impl(ldr_views* v, const int32_t* n_new, int32_t max_new
   if (max_new > 0) {
     if (launch_views_update(v->s, v->L, v->batch, v->arena, v->pos, v->G, n_new, max_new, K_new,
                             V_new, h_new, st, v->status, v->s.P ? nullptr : done,
-                            v->scratch) != hipSuccess)
+                            workspace) != hipSuccess)
       return LDR_EHIP;
     if (v->s.P && launch_views_pool(v->s, v->L, v->batch, v->arena, v->pos, n_new, max_new,
                                     K_new, V_new, st, v->status, done) != hipSuccess)
@@ -241,19 +242,8 @@ int ldr_views_init(ldr_views** out, const ldr_config* cfg, int32_t batch, void* 
   if (!v) return LDR_ENOMEM;
   v->cfg = *cfg; v->s = s; v->L = make_layout(s); v->batch = batch;
   v->arena = static_cast<uint8_t*>(arena); v->pos = pos; v->G = G; v->status = nullptr;
-  v->scratch = nullptr;
-  // One allocation: the status block, then the scratch of long updates. Without
-  // room for the scratch, updates run unsplit (the failed call's error is cleared).
-  const size_t sb = views_scratch_bytes(s, batch), fb = views_status_bytes(batch);
-  if (sb > 0) {
-    if (hipMalloc(reinterpret_cast<void**>(&v->status), fb + sb) == hipSuccess) {
-      v->scratch = reinterpret_cast<uint8_t*>(v->status) + fb;
-    } else {
-      v->status = nullptr;
-      (void)hipGetLastError();
-    }
-  }
-  if (!v->status && hipMalloc(reinterpret_cast<void**>(&v->status), fb) != hipSuccess) {
+  const size_t fb = views_status_bytes(batch);
+  if (hipMalloc(reinterpret_cast<void**>(&v->status), fb) != hipSuccess) {
     delete v;
     return LDR_ENOMEM;
   }
@@ -264,7 +254,8 @@ int ldr_views_init(ldr_views** out, const ldr_config* cfg, int32_t batch, void* 
     return LDR_EHIP;
   }
   if (max_prefix > 0) {
-    const int rc = views_update_impl(v, n_prefix, max_prefix, K_prefix, V_prefix, h_boundary, st);
+    const int rc = views_update_impl(v, n_prefix, max_prefix, K_prefix, V_prefix, h_boundary,
+                                     nullptr, 0, st);
     if (rc != LDR_OK) {
       hipStreamSynchronize(st);
       ldr_views_destroy(v);
@@ -277,7 +268,20 @@ int ldr_views_init(ldr_views** out, const ldr_config* cfg, int32_t batch, void* 
 
 int ldr_views_update(ldr_views* v, const int32_t* n_new, int32_t max_new, const void* K_new,
                      const void* V_new, const void* h_new, void* stream) {
-  return views_update_impl(v, n_new, max_new, K_new, V_new, h_new,
+  return views_update_impl(v, n_new, max_new, K_new, V_new, h_new, nullptr, 0,
+                           static_cast<hipStream_t>(stream));
+}
+
+size_t ldr_views_update_workspace_bytes(const ldr_config* cfg, int32_t batch, int32_t max_new) {
+  Shape s;
+  if (batch <= 0 || max_new <= 0 || !make_shape(cfg, &s)) return 0;
+  return views_update_ws_bytes(s, batch, max_new);
+}
+
+int ldr_views_update_ws(ldr_views* v, const int32_t* n_new, int32_t max_new, const void* K_new,
+                        const void* V_new, const void* h_new, void* workspace,
+                        size_t workspace_bytes, void* stream) {
+  return views_update_impl(v, n_new, max_new, K_new, V_new, h_new, workspace, workspace_bytes,
                            static_cast<hipStream_t>(stream));
 }
 

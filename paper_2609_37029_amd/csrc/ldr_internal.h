@@ -156,10 +156,10 @@ hipError_t launch_views_update(const Shape& s, const Layout& L, int batch, void*
                                int64_t* pos, const void* G, const int32_t* n_new,
                                int max_new, const void* K_new, const void* V_new,
                                const void* h_new, hipStream_t st, int32_t* status,
-                               int32_t* done, void* scratch);
-// Scratch of the launch above for `batch` sequences (0: none needed). With null
-// scratch an update's rows are not split over workgroups.
-size_t views_scratch_bytes(const Shape& s, int batch);
+                               int32_t* done, void* ws);
+// Workspace of the launch above (0: none needed). With null ws an update's rows
+// are not split over workgroups.
+size_t views_update_ws_bytes(const Shape& s, int batch, int max_new);
 // Mean-pooled summary banks (views.hip); runs after the update, before the
 // commit (done as above).
 hipError_t launch_views_pool(const Shape& s, const Layout& L, int batch, void* arena,

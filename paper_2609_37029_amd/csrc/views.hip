@@ -322,7 +322,7 @@ __global__ void __launch_bounds__(kThreads) views_update_kernel(UpdateArgs a) {
 // Long updates of few sequences (prefill) leave most CUs without work at one
 // workgroup per (group, layer, sequence), so the rows are then also cut into
 // `splits` ranges of whole tiles: each workgroup writes its (m, l, O) to the
-// handle's scratch and views_commit_merge_kernel combines them in order.
+// caller's workspace and views_commit_merge_kernel combines them in order.
 //
 // What bounds it: the rows' stream from HBM once the loads run ahead of the
 // tiles. Qwen3-8B shape, a 4096-row chunk
@@ -855,9 +855,9 @@ int views_splits(const Shape& s, int batch, int max_new) {
   return sp > 1 ? (int)sp : 1;
 }
 
-size_t views_scratch_bytes(const Shape& s, int batch) {
+size_t views_update_ws_bytes(const Shape& s, int batch, int max_new) {
   if (!s.learned || !views_rows_waves(s)) return 0;
-  const int sp = views_splits(s, batch, 0x7fffffff);
+  const int sp = views_splits(s, batch, max_new);
   return sp > 1 ? (size_t)s.hkv * s.D * batch * sp * s.rep * s.R * (s.d + 2) * sizeof(float) : 0;
 }
 
@@ -887,7 +887,7 @@ hipError_t launch_views_update(const Shape& s, const Layout& L, int batch, void*
                                int64_t* pos, const void* G, const int32_t* n_new,
                                int max_new, const void* K_new, const void* V_new,
                                const void* h_new, hipStream_t st, int32_t* status,
-                               int32_t* done, void* scratch) {
+                               int32_t* done, void* ws) {
   UpdateArgs a;
   a.arena = static_cast<uint8_t*>(arena); a.stride = L.stride;
   a.kw = L.kw; a.vw = L.vw; a.m = L.m; a.eta = L.eta; a.h = L.h;
@@ -906,14 +906,14 @@ hipError_t launch_views_update(const Shape& s, const Layout& L, int batch, void*
   if (rows_kernel && s.learned && max_new <= kTileRows) {
     return launch_rows<1, true>(s, a, grid, st);
   } else if (rows_kernel && s.learned) {
-    const int sp = scratch ? views_splits(s, batch, max_new) : 1;
+    const int sp = ws ? views_splits(s, batch, max_new) : 1;
     const dim3 sgrid(s.hkv, s.D, batch * sp);
     a.splits = sp;
     if (sp == 1) {
       return launch_rows<4, true>(s, a, grid, st);
     } else {
       const size_t rows = (size_t)s.hkv * s.D * batch * sp * q;
-      a.part = static_cast<float*>(scratch); a.part_ml = a.part + rows * s.d;
+      a.part = static_cast<float*>(ws); a.part_ml = a.part + rows * s.d;
       const CommitTail ct = a.ct;
       a.ct.done = nullptr;   // the merge commits
       hipError_t e = launch_rows<4, true>(s, a, sgrid, st);

@@ -76,6 +76,8 @@ def _lib():
             "ldr_views_init": (ctypes.c_int, [ctypes.POINTER(P), CP, I32, P, P, P, P, I32, P, P,
                                               P, P]),
             "ldr_views_update": (ctypes.c_int, [P, P, I32, P, P, P, P]),
+            "ldr_views_update_workspace_bytes": (SZ, [CP, I32, I32]),
+            "ldr_views_update_ws": (ctypes.c_int, [P, P, I32, P, P, P, P, SZ, P]),
             "ldr_views_status": (ctypes.c_int, [P, ctypes.c_int, P]),
             "ldr_views_destroy": (None, [P]),
             "ldr_draft_step": (ctypes.c_int, [P, ctypes.POINTER(Weights), P, P, P, SZ, P]),
@@ -167,10 +169,22 @@ class Views:
         self.G = G
         self._h = ctypes.c_void_p()
         self._stream = stream
+        # the workspace of the longest update serves every shorter one
+        self._ws_bytes = _lib().ldr_views_update_workspace_bytes(ctypes.byref(self.cfg), batch,
+                                                                 (1 << 31) - 1)
 
     def init(self, n_prefix=None, K=None, V=None, h=None):
-        """ldr_views_init: reset, then (if given) ingest a first prefix chunk."""
+        """ldr_views_init: reset, then (if given) ingest a first prefix chunk (one
+        long enough for a workspace as an update of its own)."""
         maxp = 0 if K is None else K.shape[1]
+        if n_prefix is not None and self._long(maxp):
+            self.init()
+            try:
+                self.update(n_prefix, K, V, h)
+            except LdrError:
+                self.close()
+                raise
+            return self
         _check(_lib().ldr_views_init(ctypes.byref(self._h), ctypes.byref(self.cfg), self.batch,
                                      _ptr(self.arena), _ptr(self.pos), _ptr(self.G),
                                      _ptr(n_prefix), maxp, _ptr(K), _ptr(V), _ptr(h),
@@ -178,9 +192,33 @@ class Views:
         return self
 
     def update(self, n_new: torch.Tensor, K: torch.Tensor, V: torch.Tensor, h: torch.Tensor):
-        """ldr_views_update with K/V [batch][max_new][D][Hkv][d], h [batch][L_b][hidden]."""
-        _check(_lib().ldr_views_update(self._h, _ptr(n_new), K.shape[1], _ptr(K), _ptr(V),
+        """ldr_views_update with K/V [batch][max_new][D][Hkv][d], h [batch][L_b][hidden];
+        a long update of few sequences with a workspace from torch's allocator,
+        which has it back (in the order of the update's stream) on return."""
+        rows = K.shape[1]
+        ws = self._workspace() if self._long(rows) else None
+        if ws is not None:
+            _check(_lib().ldr_views_update_ws(self._h, _ptr(n_new), rows, _ptr(K), _ptr(V), _ptr(h),
+                                              _ptr(ws), self._ws_bytes, _stream(self._stream)),
+                   "ldr_views_update_ws")
+            return
+        _check(_lib().ldr_views_update(self._h, _ptr(n_new), rows, _ptr(K), _ptr(V),
                                        _ptr(h), _stream(self._stream)), "ldr_views_update")
+
+    def _long(self, rows: int) -> bool:
+        """Updates that take a workspace (none has one below 256 rows)."""
+        return rows >= 256 and self._ws_bytes > 0
+
+    def _workspace(self):
+        """A workspace for one update on its stream; None where memory is short (the
+        update then runs without)."""
+        try:
+            if self._stream is None:
+                return torch.empty(self._ws_bytes, dtype=torch.uint8, device=self.arena.device)
+            with torch.cuda.stream(self._stream):
+                return torch.empty(self._ws_bytes, dtype=torch.uint8, device=self.arena.device)
+        except torch.cuda.OutOfMemoryError:
+            return None
 
     def status(self, clear: bool = False) -> int:
         return _lib().ldr_views_status(self._h, int(clear), _stream(self._stream))

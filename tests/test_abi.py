@@ -73,6 +73,22 @@ def test_workspace_grows_with_batch(L):
     assert L.workspace_bytes(s, 0) == 0
 
 
+def test_update_workspace(L):
+    """None for short updates, many sequences and the kernels that do not cut
+    the rows; ranges x queries x (d + 2) floats otherwise."""
+    s = synth.QWEN3_8B
+    size = L.lib().ldr_views_update_workspace_bytes
+    c = ctypes.byref(L.config(s))
+    per = s.n_layers * s.n_q_heads * s.summary * (s.head_dim + 2) * 4
+    assert size(c, 1, 255) == 0 and size(c, 1, 256) == 2 * per
+    assert size(c, 1, 4096) == 12 * per and size(c, 2, 1 << 30) == 2 * 6 * per
+    assert size(c, 16, 4096) == 0 and size(c, 0, 4096) == 0 and size(c, 1, -1) == 0
+    for shape in (synth.TINY, synth.QWEN3_8B_POOLED):
+        assert size(ctypes.byref(L.config(shape)), 1, 4096) == 0
+    assert L.lib().ldr_views_update_ws(None, None, 17, None, None, None, None, 0, None) == \
+        L.LDR_EINVAL
+
+
 def test_host_validation_needs_no_gpu(L):
     lib = L.lib()
     h = ctypes.c_void_p()

@@ -88,6 +88,61 @@ def test_row_tiles_and_ranges(gpu_lib, hq, d, drop):
     assert p.views.status() == 0
 
 
+def test_long_update_without_a_workspace(gpu_lib):
+    """One workgroup per (group, layer, sequence) walks all rows: the same copies,
+    and the summary to fp32 sums in another order."""
+    s = MINI_BF16
+    G = synth.make_G(s, device="cuda")
+    a, b = (Pair(gpu_lib, s, 2, G) for _ in range(2))
+    L = gpu_lib.lib()
+    for i, n in enumerate([(1000, 300), (513, 1000)]):
+        K, V, h = synth.decode_rows(s, 2, 1000, i, device="cuda")
+        nt = torch.tensor(n, dtype=torch.int32, device="cuda")
+        a.ingest(n, K, V, h)
+        ptr = [t.data_ptr() for t in (nt, K, V, h)]
+        st = torch.cuda.current_stream().cuda_stream
+        ws = torch.empty(64, dtype=torch.uint8, device="cuda")
+        for w, sz in ((ws.data_ptr(), 64), (ws.data_ptr() + 8, 1 << 40)):   # short; misaligned
+            assert L.ldr_views_update_ws(b.views.handle, ptr[0], 1000, *ptr[1:], w, sz,
+                                         st) == gpu_lib.LDR_EINVAL
+        assert L.ldr_views_update(b.views.handle, ptr[0], 1000, *ptr[1:], st) == 0
+        check_views(a, atol_m=2.0 ** -17)
+        b.ost = a.ost
+        check_views(b, atol_m=2.0 ** -17)   # as test_row_tiles_and_ranges
+
+
+def test_long_updates_on_a_stream_of_their_own(gpu_lib):
+    """The workspace belongs to the handle's stream; a long first prefix."""
+    s = MINI_BF16
+    G = synth.make_G(s, device="cuda")
+    a = Pair(gpu_lib, s, 2, G)
+    rows = [synth.decode_rows(s, 2, 1000, i, device="cuda") for i in range(2)]
+    n = torch.tensor([1000, 700], dtype=torch.int32, device="cuda")
+    for K, V, h in rows:
+        a.ingest([1000, 700], K, V, h)
+    check_views(a, atol_m=2.0 ** -17)
+    v = gpu_lib.Views(s, 2, G, stream=torch.cuda.Stream())
+    torch.cuda.synchronize()
+    v.init(n, *rows[0])
+    v.update(n, *rows[1])
+    torch.cuda.synchronize()
+    assert torch.equal(v.pos, a.views.pos)
+    for x, y in zip((*v.window(), *v.summary()), (*a.views.window(), *a.views.summary())):
+        assert torch.equal(x, y)
+
+
+def test_handles_hold_no_workspace(gpu_lib):
+    """A handle's own device memory is its status block, whatever its shape."""
+    vs = [gpu_lib.Views(synth.QWEN3_8B, 1, synth.make_G(synth.QWEN3_8B, device="cuda"))
+          for _ in range(16)]
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for v in vs:
+        v.init()
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] <= 16 * (2 << 20)   # pages of 2 MB at most
+
+
 def test_infinite_value_and_nan_key(gpu_lib):
     """An infinite value in the last, ragged tile leaves the summary of its
     group's heads not finite in that dimension only (infinite, or NaN where the
