@@ -667,13 +667,17 @@ __global__ void __launch_bounds__(256) views_commit_merge_kernel(UpdateArgs a) {
 // be recycled by the same update). Slots are the bank rows after the window
 // rows of the (layer, group) region: K row-major, V transposed, like the window.
 //
-// The chunks of a bank are independent: a team of d / EPC threads (16 bytes of K
-// and of V each) sums one chunk, and the teams of a workgroup take runs of
+// The chunks of a bank are independent: a team of d / EPC threads (EPC elements of
+// K and of V each) sums one chunk, and the teams of a workgroup take runs of
 // consecutive chunks, whose V means go through LDS so that the slots of a
 // dimension are written side by side (each team writing its own column, 2 bytes
-// a line, took 268 us for 1000 rows of 16 sequences, 178 now). The first
-// and the last chunk of a bank are in one run: the first may continue from the
-// stored sums of the open chunk, which the last replaces after the barrier.
+// a line, took 268 us for 1000 rows of 16 sequences, 178 now). EPC is 16 bytes,
+// or 2 elements where the launch leaves room for the two to four times as many
+// threads (a decode step of few sequences): a thread's chain of conversions, sums
+// and divisions is then that much shorter (17 rows of one sequence 7.4 -> 5.1 us,
+// of 16 sequences the whole update 21.4 -> 16.9). The first and the last chunk of
+// a bank are in one run: the first may continue from the stored sums of the open
+// chunk, which the last replaces after the barrier.
 struct PoolArgs {
   uint8_t* arena; size_t stride, kw, vw, ps;
   const int64_t* pos; const int32_t* n_new; int max_new;
@@ -689,17 +693,28 @@ __device__ inline int64_t div_pos(int64_t x, int y) {
 }
 __device__ inline int mod_pos(int64_t x, int y) { return (int)(x - div_pos(x, y) * y); }
 
-template <typename T>
+template <int BYTES> struct Piece;   // so many bytes as a native vector
+template <> struct Piece<16> { typedef u32x4 type; };
+template <> struct Piece<8> { typedef uint32_t type __attribute__((ext_vector_type(2))); };
+template <> struct Piece<4> { typedef uint32_t type; };
+
+template <typename T, int EPC>   // EPC: elements a thread
 __device__ __forceinline__ void views_pool_body(const PoolArgs& a) {
-  constexpr int EPC = 16 / sizeof(T), U = 8;   // elements a thread; rows in flight
+  typedef typename Piece<EPC * sizeof(T)>::type P;
+  constexpr int U = 8;   // rows in flight
   constexpr int kMaxTeams = kThreads / (64 / EPC);
-  __shared__ __attribute__((aligned(16))) T Vs[kThreads * EPC];   // [team][d]
+  // [team][d], rows padded by EPC: a column's reads spread over the banks
+  __shared__ __attribute__((aligned(16))) T Vs[(kThreads + kMaxTeams) * EPC];
   __shared__ int slots[kMaxTeams];
   const int g = blockIdx.x, j = blockIdx.y, b = blockIdx.z / a.zc, z = blockIdx.z - b * a.zc;
   const int n = a.n_new[b];
   if (n <= 0 || n > a.max_new) return;   // empty set: identity; bad count: commit flags it
-  const int d = a.d, tw = d / EPC, teams = kThreads / tw;   // threads of a team; teams
-  const int team = (int)threadIdx.x / tw, e = (int)threadIdx.x % tw * EPC;
+  // threads of a team and teams, both powers of two (d is 64 or 128): shifts,
+  // since a division by a value known only at run time is some thirty instructions
+  // and there were two for every V element written
+  const int d = a.d, tw = d / EPC, lw = __builtin_ctz(tw);
+  const int lt = __builtin_ctz(kThreads) - lw, teams = 1 << lt;
+  const int team = (int)threadIdx.x >> lw, e = ((int)threadIdx.x & (tw - 1)) * EPC;
   const int64_t t = a.pos[b];
   uint8_t* seq = a.arena + (size_t)b * a.stride;
   const size_t grp = (size_t)j * a.hkv + g;
@@ -717,7 +732,7 @@ __device__ __forceinline__ void views_pool_body(const PoolArgs& a) {
     const int S = bank ? a.S1 : a.S0;
     const int64_t c0 = div_pos(t, S), c1 = div_pos(t + n - 1, S);
     const int64_t cfirst = c0 > c1 - a.P + 1 ? c0 : c1 - a.P + 1;
-    const int items = (int)(c1 - cfirst) + 1, runs = (items + teams - 1) / teams;
+    const int items = (int)(c1 - cfirst) + 1, runs = (items + teams - 1) >> lt;
     float* ps = reinterpret_cast<float*>(seq + a.ps) + (grp * 2 + bank) * 2 * d + e;   // K, V sums
     for (; run < runs; run += a.zc) {
       // items: the first chunk, the last, then the ones between
@@ -732,12 +747,12 @@ __device__ __forceinline__ void views_pool_body(const PoolArgs& a) {
 #pragma unroll
         for (int i = 0; i < EPC; ++i) { sk[i] = carry ? ps[i] : 0.f; sv[i] = carry ? ps[d + i] : 0.f; }
         for (int p0 = f0; p0 < f1; p0 += U) {
-          u32x4 kx[U], vx[U];
+          P kx[U], vx[U];
 #pragma unroll
           for (int u = 0; u < U; ++u) {   // rows past the chunk repeat its last one (not added)
             const size_t row = (size_t)min(p0 + u, f1 - 1) * rstride;
-            kx[u] = *reinterpret_cast<const u32x4*>(Kn + row);
-            vx[u] = *reinterpret_cast<const u32x4*>(Vn + row);
+            kx[u] = *reinterpret_cast<const P*>(Kn + row);
+            vx[u] = *reinterpret_cast<const P*>(Vn + row);
           }
           __builtin_amdgcn_sched_barrier(0);   // all loads of the round are in flight
 #pragma unroll
@@ -755,7 +770,7 @@ __device__ __forceinline__ void views_pool_body(const PoolArgs& a) {
         }
         const float cnt = (float)(r1 - c * S);
         const int slot = a.Wr + bank * a.P + mod_pos(c, a.P);
-        uint4 ko, vo;
+        P ko, vo;
         T* kq = reinterpret_cast<T*>(&ko);
         T* vq = reinterpret_cast<T*>(&vo);
 #pragma unroll
@@ -763,8 +778,8 @@ __device__ __forceinline__ void views_pool_body(const PoolArgs& a) {
           Elem<T>::store(kq + i, sk[i] / cnt);
           Elem<T>::store(vq + i, sv[i] / cnt);
         }
-        *reinterpret_cast<uint4*>(Kw + (size_t)slot * d + e) = ko;
-        *reinterpret_cast<uint4*>(&Vs[team * d + e]) = vo;
+        *reinterpret_cast<P*>(Kw + (size_t)slot * d + e) = ko;
+        *reinterpret_cast<P*>(&Vs[team * (d + EPC) + e]) = vo;
         if (e == 0) slots[team] = slot;
       } else if (e == 0) {
         slots[team] = -1;
@@ -774,19 +789,22 @@ __device__ __forceinline__ void views_pool_body(const PoolArgs& a) {
 #pragma unroll
         for (int i = 0; i < EPC; ++i) { ps[i] = sk[i]; ps[d + i] = sv[i]; }
       }
-      for (int i = threadIdx.x; i < teams * d; i += kThreads) {   // lanes take the run's slots
-        const int slot = slots[i % teams];
-        if (slot >= 0) Vw[(size_t)(i / teams) * a.Wx + slot] = Vs[(i % teams) * d + i / teams];
-      }
+      const int col = (int)threadIdx.x & (teams - 1), vslot = slots[col];
+      if (vslot >= 0)   // lanes take the run's slots
+        for (int k = (int)threadIdx.x >> lt; k < d; k += tw)
+          Vw[(size_t)k * a.Wx + vslot] = Vs[col * (d + EPC) + k];
       __syncthreads();
     }
     run -= runs;
   }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kThreads) views_pool_kernel(PoolArgs a) {
-  views_pool_body<T>(a);
+// 4 waves a SIMD: one register more than they allow costs up to 4% of 17 to 64
+// rows of many sequences (64 of 64 rows: 129.0 us at 3)
+template <typename T, int EPC>
+__global__ void __launch_bounds__(kThreads)
+    __attribute__((amdgpu_waves_per_eu(EPC == 2 ? 6 : 4))) views_pool_kernel(PoolArgs a) {
+  views_pool_body<T, EPC>(a);
   commit_tail(a.ct, blockIdx.z / a.zc);
 }
 
@@ -943,20 +961,28 @@ hipError_t launch_views_pool(const Shape& s, const Layout& L, int batch, void* a
   a.V_new = V_new; a.D = s.D; a.hkv = s.hkv; a.d = s.d; a.Wr = s.Wr; a.Wx = s.Wx; a.P = s.P;
   a.S0 = s.S0; a.S1 = s.S1;
   // workgroups per (group, layer, sequence): one per run of chunks the rows can
-  // touch, at most about 8 workgroups per CU in all
-  const int teams = kThreads / (s.d * (int)s.el / 16);
+  // touch, at most about 8 workgroups per CU in all. 2 elements a thread while
+  // the runs of those smaller teams stay within that and the rows are few (300
+  // rows of one sequence, chunks of 64: 27.3 us against 26.8)
   const int c0 = max_new / s.S0 + 1, c1 = max_new / s.S1 + 1;
-  const long runs = ((c0 < s.P ? c0 : s.P) + teams - 1) / teams +
-                    ((c1 < s.P ? c1 : s.P) + teams - 1) / teams;
-  const long cap = 2048 / ((long)s.hkv * s.D * batch);
+  auto runs_of = [&](int epc) -> long {
+    const int teams = kThreads / (s.d / epc);
+    return ((c0 < s.P ? c0 : s.P) + teams - 1) / teams + ((c1 < s.P ? c1 : s.P) + teams - 1) / teams;
+  };
+  const long units = (long)s.hkv * s.D * batch, cap = 2048 / units;
+  const bool narrow = max_new <= 2 * kTileRows && units * runs_of(2) <= 2048;
+  const long runs = runs_of(narrow ? 2 : 16 / (int)s.el);
   const long zc = runs < cap ? runs : cap;
   a.zc = zc > 1 ? (int)zc : 1;
   const dim3 grid(s.hkv, s.D, batch * a.zc), block(kThreads);
   a.ct = CommitTail{done, (int)(grid.x * grid.y) * a.zc, pos, n_new, max_new, status};
-  if (s.dtype == LDR_BF16)
-    hipLaunchKernelGGL(views_pool_kernel<uint16_t>, grid, block, 0, st, a);
-  else
-    hipLaunchKernelGGL(views_pool_kernel<float>, grid, block, 0, st, a);
+  if (s.dtype == LDR_BF16) {
+    if (narrow) hipLaunchKernelGGL((views_pool_kernel<uint16_t, 2>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((views_pool_kernel<uint16_t, 8>), grid, block, 0, st, a);
+  } else {
+    if (narrow) hipLaunchKernelGGL((views_pool_kernel<float, 2>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((views_pool_kernel<float, 4>), grid, block, 0, st, a);
+  }
   return hipGetLastError();
 }
 

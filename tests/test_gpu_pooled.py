@@ -115,3 +115,15 @@ def test_pooled_chunks_shared_by_teams(gpu_lib, batch, strides):
         K, V, h = synth.decode_rows(s, batch, n, i, device="cuda")
         p.ingest([max(0, n - b % 3) for b in range(batch)], K, V, h)
         check_views(p)
+
+
+@pytest.mark.parametrize("shape", [MINI_BF16_POOLED, synth.TINY_POOLED])
+def test_pooled_short_updates_of_many_sequences(gpu_lib, shape):
+    """Teams of 16-byte pieces on a few rows: so many sequences that teams of
+    2-element pieces would not all be resident."""
+    batch = 600
+    p = Pair(gpu_lib, shape, batch, None, oracle_seqs=[0, batch - 1])
+    for i, n in enumerate((5, 17, 2, 40)):
+        K, V, h = synth.decode_rows(shape, batch, n, i, device="cuda")
+        p.ingest([max(0, n - b % 3) for b in range(batch)], K, V, h)
+        check_views(p)
