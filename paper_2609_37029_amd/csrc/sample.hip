@@ -222,11 +222,18 @@ __device__ inline float support_chunk_mass(const TopK& sel, const float (&x)[4],
 // 49 us for this launch (3.2 TB/s; half of it the pass over the row).
 // Beyond k = 256 the candidate chunks outgrow the registers; the radix kernel
 // stays for those.
+// More rows than CUs, each of at most kSelCap chunks (8192 tokens), go to
+// workgroups of 256 threads that take every chunk as a candidate: 3. and 4. alone.
+// Of 1024 threads, whose registers and counts are sized for long rows, two rows
+// fit a CU at a time and a step of the search is mostly its barrier (2048 rows of
+// 5003 tokens, k = 20: the call 216 us with 1024 threads, 201 with the radix
+// kernel, 110 with 256). Up to 256 rows the two differ by less than 2 us.
 constexpr int kSelMaxK = 256, kSelMaxChunks = 14336, kSelCap = 512;
 
-template <bool VEC>
-__global__ void __launch_bounds__(kSelThreads) topk_chunks_kernel(SampleArgs a, int k, TopK* sel) {
-  constexpr int KPT = kSelMaxChunks / kSelThreads, EPT = kSelCap * kChunk / kSelThreads;
+template <bool VEC, int NT>   // NT: kSelThreads, or 256 for at most kSelCap chunks
+__global__ void __launch_bounds__(NT) topk_chunks_kernel(SampleArgs a, int k, TopK* sel) {
+  constexpr bool ALL = NT < kSelThreads;   // every chunk is a candidate
+  constexpr int KPT = kSelMaxChunks / kSelThreads, EPT = kSelCap * kChunk / NT;
   extern __shared__ uint32_t mx[];   // [nch] chunk maxima, then the candidate chunks
   __shared__ int cnt[3], s_nc;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -237,7 +244,7 @@ __global__ void __launch_bounds__(kSelThreads) topk_chunks_kernel(SampleArgs a, 
   if (tid < 3) cnt[tid] = 0;
   if (tid == 3) s_nc = 0;
 
-  {  // 1. chunk maxima: 4 lanes hold a chunk, 4 tokens each
+  if constexpr (!ALL) {  // 1. chunk maxima: 4 lanes hold a chunk, 4 tokens each
     constexpr int U = 4, kSweep = kSelThreads * 4;
     auto load = [&](int v, float (&x)[4]) {
       if constexpr (VEC) {   // V % 4 == 0, v at most V - 4
@@ -265,12 +272,6 @@ __global__ void __launch_bounds__(kSelThreads) topk_chunks_kernel(SampleArgs a, 
     }
   }
   __syncthreads();
-  uint32_t key[KPT];
-#pragma unroll
-  for (int i = 0; i < KPT; ++i) {
-    const int c = tid + i * kSelThreads;
-    key[i] = c < nch ? mx[c] : 0u;
-  }
   // workgroup-wide count of pred over N values a thread; uniform, one barrier
   int turn = 0;
   auto count = [&](auto n_tag, auto&& pred) -> int {
@@ -287,52 +288,61 @@ __global__ void __launch_bounds__(kSelThreads) topk_chunks_kernel(SampleArgs a, 
   using NK = std::integral_constant<int, KPT>;
   using NE = std::integral_constant<int, EPT>;
 
-  // 2. t0: chunks with a maximum >= t0 hold the support
-  uint32_t t0 = 0u;
   int nc = nch;
-  const int enough = 64 + 2 * k < kSelCap ? 64 + 2 * k : kSelCap;
-  for (int bit = 31; bit >= 0 && nc > enough; --bit) {
-    const uint32_t t = t0 | (1u << bit);
-    const int c = count(NK{}, [&](int i) { return key[i] >= t; });
-    if (c >= k) { t0 = t; nc = c; }
-  }
-
-  if (nc > kSelCap) {   // ties: the general selection, then every chunk's log-mass
-    const TopK t = radix_select(z, V, k);
-    if (tid == 0) sel[r] = t;
-    if (L)
-      for (int vb = 4 * tid; vb < (V + 15) / 16 * 16; vb += 4 * kSelThreads) {
-        float x[4];
+  if constexpr (!ALL) {
+    uint32_t key[KPT];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = vb + i < V ? z[vb + i] : -INFINITY;
-        const float l = support_chunk_mass(t, x, vb, V, a.T);
-        if ((tid & 3) == 0) L[vb / kChunk] = l;
-      }
-    return;
-  }
+    for (int i = 0; i < KPT; ++i) {
+      const int c = tid + i * kSelThreads;
+      key[i] = c < nch ? mx[c] : 0u;
+    }
+    // 2. t0: chunks with a maximum >= t0 hold the support
+    uint32_t t0 = 0u;
+    const int enough = 64 + 2 * k < kSelCap ? 64 + 2 * k : kSelCap;
+    for (int bit = 31; bit >= 0 && nc > enough; --bit) {
+      const uint32_t t = t0 | (1u << bit);
+      const int c = count(NK{}, [&](int i) { return key[i] >= t; });
+      if (c >= k) { t0 = t; nc = c; }
+    }
 
-  // the candidate chunks, in any order; the others have no support token
+    if (nc > kSelCap) {   // ties: the general selection, then every chunk's log-mass
+      const TopK t = radix_select(z, V, k);
+      if (tid == 0) sel[r] = t;
+      if (L)
+        for (int vb = 4 * tid; vb < (V + 15) / 16 * 16; vb += 4 * kSelThreads) {
+          float x[4];
 #pragma unroll
-  for (int i = 0; i < KPT; ++i) {
-    const int c = tid + i * kSelThreads;
-    const bool in = c < nch && key[i] >= t0;
-    const uint64_t m = __ballot(in);
-    int at = 0;
-    if (lane == 0 && m) at = atomicAdd(&s_nc, __popcll(m));
-    at = __shfl(at, 0);
-    if (in) cand[at + __popcll(m & ((1ull << lane) - 1ull))] = c;
-    else if (L && c < nch) L[c] = -INFINITY;
+          for (int i = 0; i < 4; ++i) x[i] = vb + i < V ? z[vb + i] : -INFINITY;
+          const float l = support_chunk_mass(t, x, vb, V, a.T);
+          if ((tid & 3) == 0) L[vb / kChunk] = l;
+        }
+      return;
+    }
+
+    // the candidate chunks, in any order; the others have no support token
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {
+      const int c = tid + i * kSelThreads;
+      const bool in = c < nch && key[i] >= t0;
+      const uint64_t m = __ballot(in);
+      int at = 0;
+      if (lane == 0 && m) at = atomicAdd(&s_nc, __popcll(m));
+      at = __shfl(at, 0);
+      if (in) cand[at + __popcll(m & ((1ull << lane) - 1ull))] = c;
+      else if (L && c < nch) L[c] = -INFINITY;
+    }
+    __syncthreads();
   }
-  __syncthreads();
+  auto chunk_of = [&](int ci) { return ALL ? ci : cand[ci]; };
 
   // 3. the k-th largest key of their tokens
   uint32_t ek[EPT];
   int ev[EPT];   // token, -1: none
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    const int e = tid + i * kSelThreads, ci = e / kChunk;
+    const int e = tid + i * NT, ci = e / kChunk;
     int v = -1;
-    if (ci < nc) v = cand[ci] * kChunk + (e & (kChunk - 1));
+    if (ci < nc) v = chunk_of(ci) * kChunk + (e & (kChunk - 1));
     if (v >= V) v = -1;
     ev[i] = v;
     ek[i] = v >= 0 ? order_key(z[v]) : 0u;
@@ -359,8 +369,8 @@ __global__ void __launch_bounds__(kSelThreads) topk_chunks_kernel(SampleArgs a, 
   if (tid == 0) sel[r] = t;
   // 4. log-masses of the candidate chunks
   if (L)
-    for (int i = tid; i < nc * 4; i += kSelThreads) {
-      const int c = cand[i >> 2], v = c * kChunk + (i & 3) * 4;
+    for (int i = tid; i < nc * 4; i += NT) {
+      const int c = chunk_of(i >> 2), v = c * kChunk + (i & 3) * 4;
       float x[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) x[q] = v + q < V ? z[v + q] : -INFINITY;
@@ -905,11 +915,17 @@ hipError_t topk_support(const SampleArgs& a, int k, TopK* sel, hipStream_t st) {
                        a.vocab, k, sel, a.row_mul, a.row_add);
     return hipGetLastError();
   }
+  if (a.rows > 256 && a.nch <= kSelCap) {   // 4-byte loads at any alignment
+    hipLaunchKernelGGL((topk_chunks_kernel<false, 256>), dim3(a.rows), dim3(256), 0, st, a, k, sel);
+    return hipGetLastError();
+  }
   const size_t lds = (size_t)(a.nch + kSelCap) * 4;   // within the 64 KB a kernel gets unasked
   if (a.vec)
-    hipLaunchKernelGGL(topk_chunks_kernel<true>, dim3(a.rows), dim3(kSelThreads), lds, st, a, k, sel);
+    hipLaunchKernelGGL((topk_chunks_kernel<true, kSelThreads>), dim3(a.rows), dim3(kSelThreads), lds,
+                       st, a, k, sel);
   else
-    hipLaunchKernelGGL(topk_chunks_kernel<false>, dim3(a.rows), dim3(kSelThreads), lds, st, a, k, sel);
+    hipLaunchKernelGGL((topk_chunks_kernel<false, kSelThreads>), dim3(a.rows), dim3(kSelThreads),
+                       lds, st, a, k, sel);
   return hipGetLastError();
 }
 

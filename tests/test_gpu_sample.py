@@ -114,6 +114,18 @@ def test_top_k_by_chunk_maxima(gpu_lib, rows, vocab, k):
     _check_sample(gpu_lib, z, 0.8, k, seed=k, step=2)
 
 
+@pytest.mark.parametrize("rows,vocab,k", [(257, 8192, 50), (257, 8193, 50), (256, 8192, 50),
+                                          (257, 8177, 256), (700, 1000, 20), (300, 17, 16)])
+def test_top_k_of_many_short_rows(gpu_lib, rows, vocab, k):
+    """Both sides of the 256 rows and 8192 tokens beyond and up to which every
+    chunk is a candidate, with the rows of test_top_k_by_chunk_maxima."""
+    z = _logits(rows, vocab, rows + vocab + k)
+    z[0, :min(vocab, 3 * 16)] += 20.0
+    z[1, max(k // 2, 1):] = -float("inf")
+    z[2, ::16] = 9.0
+    _check_sample(gpu_lib, z, 0.8, k, seed=k, step=2)
+
+
 def test_top_k_ties_at_the_boundary(gpu_lib):
     # few distinct values: the k-th value is shared by many tokens, and the
     # lowest indices among them are inside
