@@ -299,8 +299,8 @@ __global__ void __launch_bounds__(kThreads) views_update_kernel(UpdateArgs a) {
 // One compute wave per 16 summary queries of the group (NW = rep * R / 16) and
 // one loader wave, which only stages the new rows, 32 at a time, by DMA
 // (global_load_lds) into a ring of NB stages, K rows then V rows, both as they
-// lie in memory. (A decode step has one tile: its compute waves stage it
-// themselves, NB = 1.) The scores are formed transposed, S^T = K G^T, so that a lane
+// lie in memory. (The one or two tiles of a short update are staged by the compute
+// waves themselves, all at once: NB = 1 or 2.) The scores are formed transposed, S^T = K G^T, so that a lane
 // holds 8 keys of one query and its probabilities are already the B operand of
 // O^T = V^T P^T (the order of the contraction index is free as long as both
 // operands share it); the V^T operand comes from the row-major V tile by
@@ -364,10 +364,13 @@ __device__ inline void merge_weights(float eta_a, float eta_n, float& wa, float&
 constexpr float kLn2 = 0.693147180559945309f, kLog2e = 1.44269504088896341f;
 
 // SUM: the learned summary is kept (otherwise only the ring and the boundary
-// are written, from the first tile that holds a surviving row on). NB = 1: the
-// update has at most one tile (a decode step).
+// are written, from the first tile that holds a surviving row on). NB = 1, 2: the
+// update has at most so many tiles (a decode step: one). With the loader wave and
+// its four stages two workgroups fit a CU, and each loads its stored (eta, m)
+// after the tiles: 33 rows of 64 sequences, on new inputs, 113 us against 91.
 template <int DH, int NW, int NB, bool SUM>
 __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
+  constexpr bool SELF = NB <= 2;   // no loader wave
   constexpr int KT = kTileRows, KS = DH / 32, NT = DH / 16, NTH = NW * 64;
   constexpr int CPR = DH / 8, ROWB = DH * 2;      // 16-byte chunks and bytes of a row
   constexpr int MAT = KT * ROWB, STAGE = 2 * MAT; // bytes of a K or V tile, of a stage
@@ -414,13 +417,13 @@ __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
           (__attribute__((address_space(3))) void*)(dst + MAT + q * 1024), 16, 0, 0);
     }
   };
-  if (NB > 1 && wave == NW) {   // the loader
+  if (!SELF && wave == NW) {   // the loader
     if (nt <= 0) return;
 #pragma unroll
     for (int st = 0; st < NB - 1; ++st) issue(st, t0 + st, 0, QI);
     int buf = NB - 1;
     for (int kt = 0; kt < nt; ++kt) {
-      wait_vmcnt<2 * QI * (NB > 1 ? NB - 2 : 0)>();   // stage kt has landed
+      wait_vmcnt<2 * QI * (SELF ? 0 : NB - 2)>();   // stage kt has landed
       __builtin_amdgcn_s_barrier();                   // and stage kt - 1 has been read
       if (ragged && kt == nt - 1) __builtin_amdgcn_s_barrier();
       issue(buf, t0 + kt + NB - 1, 0, QI);
@@ -429,13 +432,15 @@ __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
     wait_vmcnt<0>();   // no DMA outlives the workgroup
     return;
   }
-  // one tile: every wave stages its share of it
-  if constexpr (NB == 1) {
-    if (nt > 0) {   // (0: neither summary nor window)
+  // every wave stages its share of every tile (none: neither summary nor window)
+  if constexpr (SELF) {
+#pragma unroll
+    for (int st = 0; st < NB; ++st) {
+      if (st >= nt) break;
       if constexpr (QI >= NW) {
-        issue(0, t0, wave * (QI / NW), (wave + 1) * (QI / NW));
+        issue(st, t0 + st, wave * (QI / NW), (wave + 1) * (QI / NW));
       } else if (wave < QI) {
-        issue(0, t0, wave, wave + 1);
+        issue(st, t0 + st, wave, wave + 1);
       }
     }
   }
@@ -450,8 +455,8 @@ __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) gf[ks] = frag8(Gq + ks * 32);
   }
-  // the stored (eta, m): ahead of the tile in a decode step, whose time is this
-  // latency; after the tiles otherwise
+  // the stored (eta, m): ahead of the tiles in a short update, whose time is this
+  // latency; after them otherwise
   float* Mq = reinterpret_cast<float*>(seq + a.m) + (q0 + lr) * DH + lg * 4;
   float* etaq = reinterpret_cast<float*>(seq + a.eta) + q0 + lr;
   f32x4 ma[NT];
@@ -461,9 +466,9 @@ __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
 #pragma unroll
     for (int dt = 0; dt < NT; ++dt) ma[dt] = *reinterpret_cast<const f32x4*>(Mq + dt * 16);
   };
-  if constexpr (SUM && NB == 1) load_stored();
+  if constexpr (SUM && SELF) load_stored();
   BoundaryCopy bc{};
-  if (NB == 1 && a.keep_bnd) bc = boundary_load<uint16_t>(a, seq, j, g, b);
+  if (SELF && a.keep_bnd) bc = boundary_load<uint16_t>(a, seq, j, g, b);
 
   uint16_t* Kw = reinterpret_cast<uint16_t*>(seq + a.kw) + ((size_t)(j * a.hkv + g) * a.Wx) * DH;
   uint16_t* Vw = reinterpret_cast<uint16_t*>(seq + a.vw) + ((size_t)(j * a.hkv + g) * a.Wx) * DH;
@@ -480,7 +485,7 @@ __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
   int buf = 0;
   for (int kt = 0; kt < nt; ++kt) {
     const int r0 = (t0 + kt) * KT, nr = min(KT, n - r0);
-    if constexpr (NB == 1) wait_vmcnt<0>();   // own share of the tile
+    if constexpr (SELF) { if (kt == 0) wait_vmcnt<0>(); }   // own share of the tiles
     else __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));   // own LDS reads of stage kt - 1
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");   // the tile's LDS reads stay behind the barrier
@@ -562,7 +567,7 @@ __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
     }
     buf = buf == NB - 1 ? 0 : buf + 1;
   }
-  if (NB > 1 && a.keep_bnd && sp == 0) bc = boundary_load<uint16_t>(a, seq, j, g, b);
+  if (!SELF && a.keep_bnd && sp == 0) bc = boundary_load<uint16_t>(a, seq, j, g, b);
   boundary_store(bc, NTH);
   if constexpr (SUM) {
     l += __shfl_xor(l, 16);
@@ -578,7 +583,7 @@ __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
       return;
     }
     // eta_N = m + log l, m_N = O / l, merged with (eta_A, m_A) (Eq. 11)
-    if constexpr (NB > 1) load_stored();
+    if constexpr (!SELF) load_stored();
     float wa, wn, e;
     merge_weights(eta_a, m * kLn2 + logf(l), wa, wn, e);
     wn *= 1.f / l;
@@ -594,8 +599,8 @@ __device__ __forceinline__ void views_rows_body(const UpdateArgs& a) {
 }
 
 template <int DH, int NW, int NB, bool SUM>
-__global__ void __launch_bounds__((NB > 1 ? NW + 1 : NW) * 64)
-    __attribute__((amdgpu_waves_per_eu(NB > 1 ? 4 : 3)))
+__global__ void __launch_bounds__((NB > 2 ? NW + 1 : NW) * 64)
+    __attribute__((amdgpu_waves_per_eu(NB > 2 ? 4 : 3)))
 views_update_rows_kernel(UpdateArgs a) {
   views_rows_body<DH, NW, NB, SUM>(a);
   commit_tail(a.ct, blockIdx.z / a.splits);
@@ -848,11 +853,12 @@ hipError_t launch_rows(const Shape& s, const UpdateArgs& a, dim3 grid, hipStream
 #define LDR_VU(DH, NW)                                                                        \
   if (s.d == DH && views_rows_waves(s) == NW) {                                               \
     hipLaunchKernelGGL((views_update_rows_kernel<DH, NW, NB, SUM>), grid,                     \
-                       dim3((NB > 1 ? NW + 1 : NW) * 64), 0, st, a);                          \
+                       dim3((NB > 2 ? NW + 1 : NW) * 64), 0, st, a);                          \
     return hipGetLastError();                                                                 \
   }
   LDR_VU(128, 4) LDR_VU(64, 4)
-  if constexpr (SUM) { LDR_VU(128, 2) LDR_VU(128, 8) LDR_VU(64, 2) LDR_VU(64, 8) }
+  if constexpr (SUM) { LDR_VU(128, 2) LDR_VU(64, 2) }
+  if constexpr (SUM && NB != 2) { LDR_VU(128, 8) LDR_VU(64, 8) }
 #undef LDR_VU
   return hipErrorInvalidValue;
 }
@@ -921,8 +927,17 @@ hipError_t launch_views_update(const Shape& s, const Layout& L, int batch, void*
   a.ct = CommitTail{done, (int)(grid.x * grid.y), pos, n_new, max_new, status};
   const int q = s.rep * s.R;
   const bool rows_kernel = views_rows_waves(s) > 0;
+  // Two tiles without a loader wave where that lets more workgroups onto the CUs
+  // and there are more than the two per CU of the four-stage ring (Qwen3-8B
+  // shape, 33 rows: 16 sequences 24.0 -> 19.2 us, but 1 sequence 8.8 -> 10.4); the
+  // eight waves of 128 queries fill the CUs either way (Qwen3-32B shape, 64
+  // sequences: 126 us with the ring, 138 without).
+  const bool two_tiles = rows_kernel && views_rows_waves(s) <= 4 && max_new <= 2 * kTileRows &&
+                         (long)grid.x * grid.y * grid.z > 512;
   if (rows_kernel && s.learned && max_new <= kTileRows) {
     return launch_rows<1, true>(s, a, grid, st);
+  } else if (two_tiles && s.learned) {
+    return launch_rows<2, true>(s, a, grid, st);
   } else if (rows_kernel && s.learned) {
     const int sp = ws ? views_splits(s, batch, max_new) : 1;
     const dim3 sgrid(s.hkv, s.D, batch * sp);
@@ -943,8 +958,9 @@ hipError_t launch_views_update(const Shape& s, const Layout& L, int batch, void*
       return hipGetLastError();
     }
   } else if (rows_kernel) {
-    return max_new <= kTileRows ? launch_rows<1, false>(s, a, grid, st)
-                                : launch_rows<4, false>(s, a, grid, st);
+    return max_new <= kTileRows       ? launch_rows<1, false>(s, a, grid, st)
+           : two_tiles                ? launch_rows<2, false>(s, a, grid, st)
+                                      : launch_rows<4, false>(s, a, grid, st);
   }
   const int dpt = views_dims_per_thread(s);
   return s.dtype == LDR_BF16 ? launch_update_t<uint16_t>(a, dpt, grid, st)

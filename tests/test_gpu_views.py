@@ -88,6 +88,20 @@ def test_row_tiles_and_ranges(gpu_lib, hq, d, drop):
     assert p.views.status() == 0
 
 
+# more than 512 workgroups of (group, layer, sequence): two tiles without a loader
+@pytest.mark.parametrize("hq,d,drop", [(8, 128, 0), (4, 128, 0), (8, 64, 0), (8, 64, 2)])
+def test_two_tiles_of_many_sequences(gpu_lib, hq, d, drop):
+    """33 to 64 rows: ragged and empty second tiles, a window they wrap."""
+    batch = 150
+    s = MINI_BF16.replace(n_q_heads=hq, head_dim=d, drop_views=drop)
+    p = Pair(gpu_lib, s, batch, None if drop & 2 else synth.make_G(s, device="cuda"),
+             oracle_seqs=[0, 1, 2, batch - 1])
+    for i, (n, less) in enumerate([(33, 1), (64, 31), (48, 40)]):
+        K, V, h = synth.decode_rows(s, batch, n, i, device="cuda")
+        p.ingest([n - b % 3 * less if n > b % 3 * less else 0 for b in range(batch)], K, V, h)
+        check_views(p, atol_m=2.0 ** -17)   # as test_row_tiles_and_ranges
+
+
 def test_long_update_without_a_workspace(gpu_lib):
     """One workgroup per (group, layer, sequence) walks all rows: the same copies,
     and the summary to fp32 sums in another order."""
