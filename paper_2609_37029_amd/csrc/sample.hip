@@ -919,7 +919,7 @@ hipError_t topk_support(const SampleArgs& a, int k, TopK* sel, hipStream_t st) {
     hipLaunchKernelGGL((topk_chunks_kernel<false, 256>), dim3(a.rows), dim3(256), 0, st, a, k, sel);
     return hipGetLastError();
   }
-  const size_t lds = (size_t)(a.nch + kSelCap) * 4;   // within the 64 KB a kernel gets unasked
+  const size_t lds = (size_t)(a.nch + kSelCap) * 4;   // at most 58 KB: two workgroups a CU
   if (a.vec)
     hipLaunchKernelGGL((topk_chunks_kernel<true, kSelThreads>), dim3(a.rows), dim3(kSelThreads), lds,
                        st, a, k, sel);

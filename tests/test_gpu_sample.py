@@ -196,6 +196,7 @@ def _markov_case(batch, B, vocab, rank, dtype, seed, scale=0.4):
     (3, 5, 1001, 8, torch.float32, 0.7, 0),         # fp32 correction, ragged vocab
     (18, 3, 5003, 16, torch.bfloat16, 1.0, 40),     # more sequences than one LDS batch, top-k
     (2, 6, 4099, 32, torch.bfloat16, 0.0, 0),       # greedy
+    (3, 2, 321, 256, torch.float32, 1.0, 0),        # the widest rank
 ])
 def test_markov_matches_oracle(gpu_lib, batch, B, vocab, rank, dtype, T, k):
     """Corrected logits bit for bit, tokens exactly, lse and log q within fp32
@@ -232,7 +233,9 @@ def test_markov_without_correction_is_ldr_sample(gpu_lib):
 @pytest.mark.parametrize("batch,vocab,rank,dtype,T", [
     (18, 5003, 72, torch.bfloat16, 0.7),     # one entry a lane, two batches of 16 sequences
     (5, 4097, 64, torch.float32, 1.0),       # two entries a lane, a last tile of one token
-    (3, 129, 256, torch.bfloat16, 1.3), (1, 17, 8, torch.float32, 0.9)])
+    (3, 129, 256, torch.bfloat16, 1.3), (1, 17, 8, torch.float32, 0.9),
+    # fp32, one entry a lane; at rank 256 the W_c tile takes 65 KB of LDS
+    (5, 4097, 128, torch.float32, 1.0), (18, 321, 256, torch.float32, 0.8)])
 def test_markov_draws_as_ldr_sample_on_its_logits(gpu_lib, batch, vocab, rank, dtype, T):
     """The chunk log-masses formed with the correction are those of the pass
     over the corrected logits: tokens, lse and log q bit for bit."""
