@@ -480,17 +480,16 @@ __device__ void chunk_keys(const SampleArgs& a, const float* Lr, int r, int c0, 
   }
 }
 
-// Chunk log-masses of tokens [v0, v1) of one row (v0 a multiple of 16): each
+// Chunk log-masses of one row, `slice` tokens (a multiple of 16) a workgroup: each
 // lane takes 4 consecutive tokens, so 4 lanes hold a chunk. Whole groups of U
 // sweeps of kThreads * 4 tokens load without bounds checks (U loads in flight
 // per lane), the rest one guarded sweep at a time. Writes L_c for the chunks
 // it covers.
 template <bool UNIT_T, bool TOPK, bool VEC>
-__global__ void __launch_bounds__(kThreads) chunk_lse_kernel(SampleArgs a, int v_begin,
-                                                             int v_end, int slice) {
+__global__ void __launch_bounds__(kThreads) chunk_lse_kernel(SampleArgs a, int slice) {
   constexpr int U = 4, kSweep = kThreads * 4;
   const int r = blockIdx.y;
-  const int v0 = v_begin + blockIdx.x * slice, v1 = min(v_end, v0 + slice);
+  const int v0 = blockIdx.x * slice, v1 = min(a.vocab, v0 + slice);
   const float* z = a.logits + ((long)r * a.row_mul + a.row_add) * a.vocab;
   float* L = a.L + (long)r * a.ldL;
   const TopK sel = TOPK ? a.sel[r] : TopK{0u, 0};
@@ -823,15 +822,6 @@ SamplePlan sample_plan(int rows, int vocab) {
   return p;
 }
 
-int chunk_lse_slice(int rows, int ntok) {
-  // tokens per workgroup of chunk_lse_kernel: the range split evenly over
-  // max(1, 2048 / rows) workgroups per row (about 2048 in all: one round of
-  // resident workgroups), rounded up to whole sweeps of 1024 tokens
-  const int per_row = rows >= 2048 ? 1 : 2048 / rows;
-  const long even = ((long)ntok + per_row - 1) / per_row;
-  return (int)((even + 1023) / 1024 * 1024);
-}
-
 size_t sample_part_bytes(int rows, int vocab) {
   const SamplePlan p = sample_plan(rows, vocab);
   const size_t L = ((size_t)rows * p.ldL * sizeof(float) + 255) / 256 * 256;
@@ -886,13 +876,16 @@ SampleArgs sample_args(const float* logits, int rows, int vocab, float temperatu
   return a;
 }
 
-hipError_t chunk_lse(const SampleArgs& a, int v0, int v1, hipStream_t st) {
-  if (v0 >= v1) return hipSuccess;
-  const int slice = chunk_lse_slice(a.rows, v1 - v0);
-  const dim3 grid((unsigned)((v1 - v0 + slice - 1) / slice), (unsigned)a.rows);
+// The row split evenly over max(1, 2048 / rows) workgroups (about 2048 in all: one
+// round of resident workgroups), rounded up to whole sweeps of 1024 tokens.
+hipError_t chunk_lse(const SampleArgs& a, hipStream_t st) {
+  const int per_row = a.rows >= 2048 ? 1 : 2048 / a.rows;
+  const long even = ((long)a.vocab + per_row - 1) / per_row;
+  const int slice = (int)((even + 1023) / 1024 * 1024);
+  const dim3 grid((unsigned)(((long)a.vocab + slice - 1) / slice), (unsigned)a.rows);
   const bool unit = a.T == 1.f, topk = a.sel != nullptr;
 #define LDR_CL(U, K, V) \
-  hipLaunchKernelGGL((chunk_lse_kernel<U, K, V>), grid, dim3(kThreads), 0, st, a, v0, v1, slice)
+  hipLaunchKernelGGL((chunk_lse_kernel<U, K, V>), grid, dim3(kThreads), 0, st, a, slice)
   if (a.vec) {
     if (unit) { if (topk) LDR_CL(true, true, true); else LDR_CL(true, false, true); }
     else { if (topk) LDR_CL(false, true, true); else LDR_CL(false, false, true); }
@@ -965,16 +958,10 @@ hipError_t launch_sample(const float* logits, int rows, int vocab, float tempera
       a.sel = sel;
       if (topk_in_chunks(a, top_k)) return sample_finish(a, tokens, lse, logq, st);
     }
-    const hipError_t e = chunk_lse(a, 0, vocab, st);
+    const hipError_t e = chunk_lse(a, st);
     if (e != hipSuccess) return e;
   }
   return sample_finish(a, tokens, lse, logq, st);
-}
-
-hipError_t launch_chunk_lse(const float* logits, int rows, int vocab, float temperature, void* ws,
-                            int v0, int v1, hipStream_t st) {
-  if (temperature <= 0.f || v0 < 0 || v1 > vocab || v0 % kChunk) return hipErrorInvalidValue;
-  return chunk_lse(sample_args(logits, rows, vocab, temperature, 0, 0, ws, 1, 0), v0, v1, st);
 }
 
 hipError_t launch_sample_finish(const float* logits, int rows, int vocab, float temperature,
