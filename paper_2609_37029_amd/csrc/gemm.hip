@@ -6,8 +6,8 @@
 // batch x B rows: loader waves stage the weights through LDS by DMA while
 // compute waves read the activation rows straight into MFMA fragments
 // (frag_gemm below, tiles of 16 to 256 rows); the vocabulary head above 64 rows
-// has a kernel of its own (gemm_tiled_kernel). fp32: a plain SIMT tile kernel
-// with the same epilogues.
+// has a kernel of its own (gemm_tiled_kernel). fp32 (gemm_f32_kernel): fp32 MFMA
+// on operands loaded straight into registers, with the same epilogues.
 //
 // Epilogues: EPI_STORE writes fp32 (split-K partials); EPI_LOGITS writes the
 // fp32 logits; EPI_SWIGLU reads the gate and up rows of w_gate_up interleaved
@@ -143,11 +143,9 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, int n0, int m0, in
 // linear ids are renumbered so that XCD c takes the c-th eighth of the tiles
 // in (z, x, y) order. A K split's activation columns are then read into one
 // or two XCDs' L2 instead of all eight, and the row tiles of one column tile
-// (M above one tile) share their weight columns in one L2. Returns the place in
-// that order, and the XCD, of the first row tile of this column tile and split:
-// the same for all of its row tiles.
-struct ColumnPlace { int l, xcd; };
-__device__ __forceinline__ ColumnPlace xcd_tile(int& x, int& y, int& z) {
+// (M above one tile) share their weight columns in one L2. Returns l, the tile's
+// place in that order.
+__device__ __forceinline__ int xcd_tile(int& x, int& y, int& z) {
   const int gx = gridDim.x, gy = gridDim.y;
   const int total = gx * gy * gridDim.z;
   const int lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
@@ -156,11 +154,7 @@ __device__ __forceinline__ ColumnPlace xcd_tile(int& x, int& y, int& z) {
   y = l % gy;
   x = (l / gy) % gx;
   z = l / (gx * gy);
-  // the XCD of place l - y (the inverse of l above): this one's own for the first row tile
-  const int l0 = l - y, cut = r * (q + 1);
-  int xcd = c;
-  if (y > 0) xcd = l0 < cut ? l0 / (q + 1) : r + (l0 - cut) / q;
-  return ColumnPlace{l0, xcd};
+  return l;
 }
 
 // fp32 on v_mfma_f32_16x16x4_f32 (full fp32 products and sums). A workgroup
@@ -334,7 +328,7 @@ __device__ __forceinline__ void frag_gemm(const GemmArgs& a) {
   __shared__ __attribute__((aligned(1024))) uint8_t Wsm[NB * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int bx, by, z;
-  const ColumnPlace cp = xcd_tile(bx, by, z);
+  const int l = xcd_tile(bx, by, z);
   const int n0 = bx * BN, m0 = by * BM;
   const int kper = a.K / a.splits, kbeg = z * kper, nk = kper / BK;
   // Workgroups start their K range at different steps and wrap around: weight
@@ -346,10 +340,22 @@ __device__ __forceinline__ void frag_gemm(const GemmArgs& a) {
   // inside it, so that the workgroups of one L2 stay near the same activation
   // columns (256 rows 1211 -> 1175 us, 1024 rows unchanged; the first rule costs
   // those 3%).
-  // All row tiles of a column tile start at the same step, whatever their number:
-  // they read the same weights side by side, and a sequence's logits do not
-  // depend on the row tile it falls in.
-  const int phase = BM <= 64 ? ((cp.l >> 3) & 7) * 8 + (cp.l & 7) : cp.xcd * 8 + ((cp.l >> 3) & 7);
+  // All row tiles of a column tile start at the same step, whatever their number,
+  // by the place and the XCD of the first of them: they read the same weights side
+  // by side, and a sequence's logits do not depend on the row tile it falls in.
+  // (The XCD of an earlier place by steps back over the XCDs' first places: a
+  // division cost every launch of a step 0.2 to 0.4 us. Up to 64 rows there is one
+  // row tile.)
+  int phase;
+  if constexpr (BM <= 64) {
+    phase = ((l >> 3) & 7) * 8 + (l & 7);
+  } else {
+    const int total = gridDim.x * gridDim.y * gridDim.z, q = total >> 3, r = total & 7;
+    const int l0 = l - by;
+    int xcd = (blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) & 7;
+    while (l0 < xcd * q + min(xcd, r)) --xcd;
+    phase = xcd * 8 + ((l0 >> 3) & 7);
+  }
   const int rot = phase * nk / 64;
   auto kstep = [&](int st) {   // the K step of stage st (past the end: the last one's)
     const int q = min(st, nk - 1) + rot;
@@ -970,7 +976,8 @@ GemmPlan plan_gemm(int dtype, int M, int N, int K, bool allow_split, bool swiglu
     // rounds over the CUs times the bytes a workgroup moves, its activation rows
     // and weight columns over its K range, and four times its output tile (fp32
     // partials are written in a burst at the end and read back by the next
-    // kernel). At 1024 rows the down projection then runs on 128 columns split
+    // kernel; the four is a fit to the plans measured best at 256 and 1024 rows of
+    // the Qwen3-8B shape). At 1024 rows the down projection then runs on 128 columns split
     // in two instead of 64 unsplit, with as many workgroups (120 -> 84 us); at 256
     // rows QKV, O and down keep 96 x 4, 64 x 4 and 128 x 8 (O at 128 x 8, the next
     // by this cost, makes its own time up in the norm that reads the partials).
