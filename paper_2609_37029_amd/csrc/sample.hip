@@ -527,10 +527,10 @@ __global__ void __launch_bounds__(kThreads) chunk_lse_kernel(SampleArgs a, int s
 
 // The chunk keys and the in-chunk draw of one row (T > 0), one workgroup of
 // kDrawThreads threads per row: the Gumbel-max over all its chunk log-masses
-// (each lane a sweep or two of 8 entries), the lanes' partials combined (max /
-// sum of exp(L) for lse, best key and chunk), then lanes 0 .. 15 of the first
-// wave take the 16 tokens of the winning chunk c (support members only), their
-// exact keys fl(fl(z_v/T) + g_v), and the first maximum is the token.
+// (12 entries a lane and sweep), the lanes' partials combined (max / sum of exp(L)
+// for lse, best key and chunk), then lanes 0 .. 15 of the first wave take the 16
+// tokens of the winning chunk c (support members only), their exact keys
+// fl(fl(z_v/T) + g_v), and the first maximum is the token.
 constexpr int kDrawThreads = 1024;
 __global__ void __launch_bounds__(kDrawThreads) chunk_draw_kernel(SampleArgs a, int32_t* tokens,
                                                                   float* lse, float* logq) {

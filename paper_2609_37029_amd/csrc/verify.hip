@@ -16,12 +16,11 @@
 //     chunk's running max and sum of exp(P / T);
 //  2. emit pass: one workgroup per (sequence, 2048 tokens). It first takes the
 //     in-order acceptance test itself (16 lanes merge a row's lse partials; a
-//     launch of its own for that is mostly the launch, and every workgroup's
-//     noise does not wait for it), then reads its part of the target row where
-//     the round stops (and of the draft row, 16-byte loads): Gumbel keys log w_v +
-//     g_v over the residual w = [p - q]_+ (every entry with w_v > 0 in fp32), and
-//     the bonus-rule keys fl(fl(P_v / T) + g_v) (the draw at a bonus, and the
-//     fallback when the residual has no positive mass);
+//     launch of its own for that is mostly the launch), then reads its part of
+//     the target row where the round stops (and of the draft row, 16-byte loads):
+//     Gumbel keys log w_v + g_v over the residual w = [p - q]_+ (every entry with
+//     w_v > 0 in fp32), and the bonus-rule keys fl(fl(P_v / T) + g_v) (the draw at
+//     a bonus, and the fallback when the residual has no positive mass);
 //  3. merge: the best key over the chunks, lower token first on ties.
 // T = 0 verifies greedily: pass 1 takes the first argmax of all B + 1 rows and
 // the merge compares them with the candidates.

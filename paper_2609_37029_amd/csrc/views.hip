@@ -325,10 +325,10 @@ __global__ void __launch_bounds__(kThreads) views_update_kernel(UpdateArgs a) {
 // caller's workspace and views_commit_merge_kernel combines them in order.
 //
 // What bounds it: the rows' stream from HBM once the loads run ahead of the
-// tiles. Qwen3-8B shape, a 4096-row chunk
-// of one sequence 350 -> 36 us (one workgroup per group and layer before), of 16
-// sequences 661 -> 319 us (4.6 TB/s; the loads alone, without any arithmetic,
-// take about as long), 17 rows of 16 sequences 20.4 -> 14.8 us.
+// tiles. Qwen3-8B shape, a 4096-row chunk of one sequence 350 -> 34 us (one
+// workgroup per group and layer before; 85 us unsplit), of 16 sequences 661 ->
+// 319 us (4.6 TB/s; the loads alone, without any arithmetic, take about as long),
+// 17 rows of 16 sequences 20.4 -> 14.8 us.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
